@@ -336,125 +336,178 @@ __global__ __launch_bounds__(kS3Threads, 2) void k_s3(BatchArgs p) {
     }
 }
 
-// ------------------------------------------------------------------ S4, one channel
-// Plain FP32 vector arithmetic for the frame sums; FP64 for the combination
-// and the chunk sums.  Partials hold (sum v, sum v^2) with
-// v = M4 - gamma (p_k p_l + 2(X^2+Y^2+U^2+V^2)), gamma = (m-1)/(m(m+1)) for the
-// k-statistic (1/m for the natural estimator).
+// ------------------------------------------------------------------ FP32 matrix cores
+// The FP32 S4 kernels run their frame sums on the matrix cores' FP32 forms
+// (v_mfma_f32_32x32x2_f32, v_mfma_f32_16x16x4_f32).  Each output is a chain of
+// fused multiply-adds over the contraction index in ascending order, rounded to
+// nearest at every step with subnormals kept: bit for bit the sum that fmaf
+// over the frames in order gives on the vector ALUs (checked on 10^6 values a
+// form, subnormal results among them).
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+typedef float floatx16_t __attribute__((ext_vector_type(16)));
+
+// x holds, in lanes 0-31 and 32-63, an earlier and a later frame's value of one
+// column set, y the same of another: afterwards x holds the earlier frame's
+// values of the first set (lanes 0-31) and of the second (lanes 32-63), y the
+// later frame's.
+__device__ __forceinline__ void swap_halves(float& x, float& y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+
+// Order this wave's own LDS accesses (wave-private scratch: no other wave's).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// ------------------------------------------------------------------ S4, one channel, FP32
+// With X = sum Re_k Re_l, Y = sum Im_k Im_l, U = sum Re_k Im_l, V = sum Im_k Re_l
+// and M4 = sum P_k P_l (FP32 sums over the frames in order), the chunk's term is
+// v = M4 - gamma (p_k p_l + 2(X^2+Y^2+U^2+V^2)) in FP64, gamma = (m-1)/(m(m+1))
+// for the k-statistic (1/m for the natural estimator); partials hold (sum v,
+// sum v^2).
+//
+// Wave w owns the 32 x 32 quadrant (32 (w / 2), 32 (w % 2)) of the 64 x 64 tile
+// with five 32x32 accumulators; one MFMA takes two frames (lanes 0-31 the
+// earlier, 32-63 the later).  Frames are staged through LDS in batches of
+// kS4FFrames (even, so that pairs never straddle a batch; missing frames are
+// zero and add nothing), two buffers, one barrier per batch.  p_k and p_l are
+// summed in frame order by one wave half each (swap_halves).
+//
+// Bound: the FP32 MFMA and the vector ALU do not overlap (probe: 4 MFMA of 64
+// cycles and 64 FP64 FMA take 570 cycles, 257 and 290 alone), so a wave and
+// chunk of 10 frames costs 25 x 64 + 16 points x 13 FP64-rate instructions x
+// 4.5 = 2500 SIMD cycles; five FMAs per point and frame on the vector ALUs
+// alone are 2800 and cost 8 LDS operands per 16 points instead of 2.  Measured
+// (10^8 samples, N = 8192, N_f = 2048, m = 10): 3.38 ms, the form on the vector
+// ALUs 8.71; 2^26 samples, N = 4096, N_f = 512: 0.34 ms against 0.77.
+constexpr int kS4FFrames = 10;
 constexpr int kS4Threads = 256;
 
-__global__ __launch_bounds__(kS4Threads, 2) void k_s4_single(BatchArgs p) {
-    __shared__ float2 sA[kFrameBatch][kTile];
-    __shared__ float2 sB[kFrameBatch][kTile];
+// ONE_BATCH: every chunk fits one frame batch (m <= 10).
+template <bool ONE_BATCH>
+__global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
+    __shared__ float2 sm[2][2][kS4FFrames][kTile];      // [buffer][side k, l][frame][column]
+    __shared__ double ps[4][64];                        // per wave: -gamma p_k (32 rows), p_l (32 columns)
 
     Block bk;
     View v;
     if (!resolve_block(p, bk, v)) return;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, w = tid >> 6;
+    const int r32 = lane & 31, kh = lane >> 5;
+    const int rowK = 32 * (w >> 1) + r32, rowL = 32 * (w & 1) + r32;
+    // loader role: wave -> (side, parity of the frames), lane -> column
+    const int side = w >> 1, half = w & 1;
+    const double gamma = p.gamma, m2g = -2.0 * gamma;
+
+    int buf = 0;
     Item it;
     while (next_item<kTile, 2>(p, bk, it)) {
     const int c0 = it.c0, c1 = it.c1;
-    const int k0 = it.k0, l0 = it.l0;
-    const float2* A = v.coef + it.ch[0] * v.cs;
+    const int gcol = (side ? it.l0 : it.k0) + lane;
+    const bool live = gcol < v.Nf;
+    const float2* src = v.coef + it.ch[0] * v.cs + gcol;
 
-    const int tid = threadIdx.x;
-    const int ti = tid >> 4, tj = tid & 15;
     double acc[16][2];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q][0] = acc[q][1] = 0.0;
+    for (int r = 0; r < 16; ++r) acc[r][0] = acc[r][1] = 0.0;
 
-    const int col = tid;
-    bool live = false;
-    const float2* src = nullptr;
-    if (col < kTile) {
-        live = k0 + col < v.Nf;
-        src = A + k0 + col;
-    } else if (col < 2 * kTile) {
-        live = l0 + col - kTile < v.Nf;
-        src = A + l0 + col - kTile;
-    }
-    const double gamma = p.gamma;
+    constexpr int kSlots = kS4FFrames / 2;
+    const int per_chunk = ONE_BATCH ? 1 : (v.m + kS4FFrames - 1) / kS4FFrames;
+    const int n_batches = (c1 - c0) * per_chunk;
+    float2 pre[kSlots];
+    auto fetch = [&](int c, int fb) {
+        const int nf = min(kS4FFrames, v.m - fb);
+        const float2* q = src + v.off + ((int64_t)c * v.m + fb) * v.K;
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int f = half + 2 * j;
+            pre[j] = (live && f < nf) ? q[(int64_t)f * v.K] : make_float2(0.f, 0.f);
+        }
+    };
+    if (n_batches > 0) fetch(c0, 0);
 
+    floatx16_t d[5];
+    float pacc = 0.f;
+    int c = c0, fb = 0;                                 // chunk and first frame of the batch
 #pragma unroll 1
-    for (int c = c0; c < c1; ++c) {
-        const int64_t fbase = v.off + (int64_t)c * v.m * v.K;
-        float X[16], Y[16], U[16], V[16], M4[16], pk[4], pl[4];
+    for (int b = 0; b < n_batches; ++b) {
+        const bool first = ONE_BATCH || fb == 0;
+        const int nf = ONE_BATCH ? v.m : min(kS4FFrames, v.m - fb);
+        const bool last = ONE_BATCH || fb + nf == v.m;
+        float2(*sA)[kTile] = sm[buf][0];
+        float2(*sB)[kTile] = sm[buf][1];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) X[q] = Y[q] = U[q] = V[q] = M4[q] = 0.f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) pk[u] = pl[u] = 0.f;
+        for (int j = 0; j < kSlots; ++j) sm[buf][side][half + 2 * j][lane] = pre[j];
+        lds_barrier();
+        buf ^= 1;
+        if (last) {
+            ++c;
+            fb = 0;
+        } else {
+            fb += kS4FFrames;
+        }
+        if (b + 1 < n_batches) fetch(c, fb);
 
-#pragma unroll 1
-        for (int fb = 0; fb < v.m; fb += kFrameBatch) {
-            const int nf = min(kFrameBatch, v.m - fb);
-            lds_barrier();
-            if (col < 2 * kTile) {
-                for (int f = 0; f < nf; ++f) {
-                    const float2 x = live ? src[fbase + (int64_t)(fb + f) * v.K] : make_float2(0.f, 0.f);
-                    if (col < kTile) sA[f][col] = x;
-                    else sB[f][col - kTile] = x;
-                }
-            }
-            lds_barrier();
-#pragma unroll 1
-            for (int f = 0; f < nf; ++f) {
-                float2 a[4], b[4];
-                float Pa[4], Pb[4];
+        if (first) {
+            pacc = 0.f;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    a[u] = sA[f][ti + 16 * u];
-                    b[u] = sB[f][tj + 16 * u];
-                    Pa[u] = a[u].x * a[u].x + a[u].y * a[u].y;
-                    Pb[u] = b[u].x * b[u].x + b[u].y * b[u].y;
-                    pk[u] += Pa[u];
-                    pl[u] += Pb[u];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const int q = u * 4 + w;
-                        X[q] += a[u].x * b[w].x;
-                        Y[q] += a[u].y * b[w].y;
-                        U[q] += a[u].x * b[w].y;
-                        V[q] += a[u].y * b[w].x;
-                        M4[q] += Pa[u] * Pb[w];
-                    }
-                }
-            }
+            for (int g = 0; g < 5; ++g) d[g] = floatx16_t{};
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int s = 0; s < kSlots; ++s) {
+            if (2 * s >= nf) break;
+            const float2 a = sA[2 * s + kh][rowK], x = sB[2 * s + kh][rowL];
+            float Pa = fmaf(a.x, a.x, a.y * a.y), Px = fmaf(x.x, x.x, x.y * x.y);
+            d[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, x.x, d[0], 0, 0, 0);     // X
+            d[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, x.y, d[1], 0, 0, 0);     // U
+            d[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, x.x, d[2], 0, 0, 0);     // V
+            d[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, x.y, d[3], 0, 0, 0);     // Y
+            d[4] = __builtin_amdgcn_mfma_f32_32x32x2f32(Pa, Px, d[4], 0, 0, 0);       // M4
+            swap_halves(Pa, Px);            // (P_k, P_l) of the earlier frame, of the later
+            pacc += Pa;
+            pacc += Px;
+        }
+        if (!last) continue;
+
+        // Register r of lane (kh, r32) is grid point
+        // k = k0 + 32 (w / 2) + 8 (r / 4) + 4 kh + r % 4, l = l0 + 32 (w % 2) + r32.
+        wave_lds_fence();
+        ps[w][lane] = kh == 0 ? -gamma * (double)pacc : (double)pacc;
+        wave_lds_fence();
+        const double pl = ps[w][32 + r32];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const int q = u * 4 + w;
-                const double x = X[q], y = Y[q], uu = U[q], vv = V[q];
-                const double sq = x * x + y * y + uu * uu + vv * vv;
-                const double val = (double)M4[q] - gamma * ((double)pk[u] * (double)pl[w] + 2.0 * sq);
-                acc[q][0] += val;
-                acc[q][1] += val * val;
-            }
+        for (int r = 0; r < 16; ++r) {
+            const double X = d[0][r], U = d[1][r], V = d[2][r], Y = d[3][r];
+            const double sq = fma(X, X, fma(Y, Y, fma(U, U, V * V)));
+            const double npk = ps[w][8 * (r >> 2) + 4 * kh + (r & 3)];
+            const double val = fma(m2g, sq, fma(npk, pl, (double)d[4][r]));
+            acc[r][0] += val;
+            acc[r][1] = fma(val, val, acc[r][1]);
         }
     }
 
     double* o = it.part;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int r = 0; r < 16; ++r) {
+        const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + rowL;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int idx = (ti + 16 * u) * kTile + tj + 16 * w;
-#pragma unroll
-            for (int comp = 0; comp < 2; ++comp) {
-                double val = acc[u * 4 + w][comp];
-                if (p.accumulate) val += o[comp * kTile * kTile + idx];
-                o[comp * kTile * kTile + idx] = val;
-            }
+        for (int comp = 0; comp < 2; ++comp) {
+            double val = acc[r][comp];
+            if (p.accumulate) val += o[comp * kTile * kTile + idx];
+            o[comp * kTile * kTile + idx] = val;
         }
     }
     }
 }
 
 // ------------------------------------------------------------------ S4, one channel, matrix cores
-// The same sums as k_s4_single, with the frame contractions on the matrix
+// The same sums as k_s4_mfma_f32, with the frame contractions on the matrix
 // cores (v_mfma_f32_32x32x16_bf16, FP32 accumulation).  Each FP32 operand x is
 // split into three bfloat16 terms x = h + m + l, each rounded to nearest
 // (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m); both differences are
@@ -485,8 +538,6 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_single(BatchArgs p) {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kMfmaFrames = 10;      // frames per operand batch: 6 x 10 = 60 <= 64 slots
@@ -1233,36 +1284,52 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
 //   sum xyzw = sum E_k F_l,  sum xy = e_k = sum E_k,  sum zw = f_l = sum F_l,
 //   sum xz = G_ac = sum a'_k c'_l,   sum yw = conj(G_bd),
 //   sum xw = H_ad = sum a'_k d'*_l,  sum yz = conj(H_bc).
-// Five complex frame sums per grid point (FP32 vector arithmetic), the
-// combination and the chunk sums in FP64.  Tiles are 32 x 32; each thread owns
-// the grid points (k0 + ti + 16u, l0 + tj + 16v), u, v < 2.
+// Five complex frame sums per grid point (FP32, over the frames in order), the
+// combination and the chunk sums in FP64.
+//
+// Each sum is a chain of fused multiply-adds, per frame first
+//   (x y).re: -Im x Im y, then Re x Re y     (x y).im: Im x Re y, then Re x Im y
+//   (x y*).re: Im x Im y, then Re x Re y     (x y*).im: -Re x Im y, then Im x Re y,
+// which v_mfma_f32_16x16x4_f32 runs with the two steps of two frames side by
+// side along its contraction dimension: lanes 16 g .. 16 g + 15 supply step
+// g % 2 of frame g / 2 of the pair (see FP32 matrix cores above: ascending
+// order, so bit for bit the chain).  Tiles are 32 x 32; wave w owns the 16 x 16
+// block (16 (w / 2), 16 (w % 2)) with ten accumulators of four registers, lane
+// (g, li) holding grid points (4 g + e, li).  Frames are staged through LDS in
+// batches of kS4FFrames, two buffers, one barrier per batch.
+//
+// Bound: per wave and chunk of 10 frames 50 MFMA of 32 cycles, 122 FP64-rate
+// instructions for the combination and ~150 to form the operands, which do not
+// overlap (same units): ~2600 SIMD cycles for 256 points, against 1040 FMAs
+// (3400 cycles) on the vector ALUs alone.  Measured (two channels, 2^22
+// samples, N = 2048, N_f = 301, m = 12, all S4 orbits): 0.57 ms at three waves
+// per SIMD, 0.63 at two; on the vector ALUs 0.83.
 constexpr int kS4XThreads = 256;
 
-__device__ __forceinline__ void cmac(float2& acc, float2 x, float2 y) {        // acc += x y
-    acc.x = fmaf(x.x, y.x, fmaf(-x.y, y.y, acc.x));
-    acc.y = fmaf(x.x, y.y, fmaf(x.y, y.x, acc.y));
-}
-__device__ __forceinline__ void cmacc(float2& acc, float2 x, float2 y) {       // acc += x conj(y)
-    acc.x = fmaf(x.x, y.x, fmaf(x.y, y.y, acc.x));
-    acc.y = fmaf(x.y, y.x, fmaf(-x.x, y.y, acc.y));
-}
-
-__global__ __launch_bounds__(kS4XThreads, 2) void k_s4_cross(BatchArgs p) {
-    __shared__ float2 sv[4][kFrameBatch][kTileX];   // a'_k, b'_k, c'_l, d'_l
+__global__ __launch_bounds__(kS4XThreads, 3) void k_s4_cross_f32(BatchArgs p) {
+    __shared__ float2 sv[2][4][kS4FFrames][kTileX];     // [buffer][a'_k, b'_k, c'_l, d'_l][frame][column]
+    __shared__ float2 ps[4][2][16];                     // per wave: e of its 16 rows, f of its 16 columns
 
     Block bk;
     View v;
     if (!resolve_block(p, bk, v)) return;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, w = tid >> 6;
+    const int g = lane >> 4, li = lane & 15;
+    const bool second = g & 1;                          // which step of a frame this lane supplies
+    const uint32_t neg_first = second ? 0u : 0x80000000u;
+    const int rowA = 16 * (w >> 1) + li, rowB = 16 * (w & 1) + li;
+    auto flip = [](float x, uint32_t m) { return __uint_as_float(__float_as_uint(x) ^ m); };
+    // loader role: wave -> array, lane half -> parity of the frames, lane -> column
+    const int arr = w, col = lane & 31, half = lane >> 5;
+    const double gamma = p.gamma;
+
+    int buf = 0;
     Item it;
     while (next_item<kTileX, 4>(p, bk, it)) {
     const int c0 = it.c0, c1 = it.c1;
-    const int k0 = it.k0, l0 = it.l0;
-
-    const int tid = threadIdx.x;
-    const int ti = tid >> 4, tj = tid & 15;
-    // Loader role: (array, column, half of the frames).
-    const int arr = (tid & 127) >> 5, col = tid & 31, half = tid >> 7;
-    const int gcol = (arr < 2 ? k0 : l0) + col;
+    const int gcol = (arr < 2 ? it.k0 : it.l0) + col;
     const bool live = gcol < v.Nf;
     // S4 planes: factors a and d at column + q, b and c at column - q
     const float2* src = v.coef + it.ch[arr] * v.cs + gcol + ((arr == 0 || arr == 3) ? p.s4_shift : -p.s4_shift);
@@ -1270,93 +1337,125 @@ __global__ __launch_bounds__(kS4XThreads, 2) void k_s4_cross(BatchArgs p) {
     double acc[4][4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-    const double gamma = p.gamma;
 
+    constexpr int kSlots = kS4FFrames / 2;
+    const int per_chunk = (v.m + kS4FFrames - 1) / kS4FFrames;
+    const int n_batches = (c1 - c0) * per_chunk;
+    float2 pre[kSlots];
+    auto fetch = [&](int c, int fb) {
+        const int nf = min(kS4FFrames, v.m - fb);
+        const float2* q = src + v.off + ((int64_t)c * v.m + fb) * v.K;
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int f = half + 2 * j;
+            pre[j] = (live && f < nf) ? q[(int64_t)f * v.K] : make_float2(0.f, 0.f);
+        }
+    };
+    if (n_batches > 0) fetch(c0, 0);
+
+    // (re, im) accumulators of E F, a c, b d, a d*, b c*
+    floatx4_t d[10];
+    float2 pacc = make_float2(0.f, 0.f);                // sums of E (lanes 0-31) and F (lanes 32-63)
+    int c = c0, fb = 0;
 #pragma unroll 1
-    for (int c = c0; c < c1; ++c) {
-        const int64_t fbase = v.off + (int64_t)c * v.m * v.K;
-        float2 sef[4], gac[4], gbd[4], had[4], hbc[4], e[2], f[2];
+    for (int b = 0; b < n_batches; ++b) {
+        const int nf = min(kS4FFrames, v.m - fb);
+        const bool first = fb == 0, last = fb + nf == v.m;
+        const float2(*sb)[kS4FFrames][kTileX] = sv[buf];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sef[q] = gac[q] = gbd[q] = had[q] = hbc[q] = make_float2(0.f, 0.f);
-        e[0] = e[1] = f[0] = f[1] = make_float2(0.f, 0.f);
-#pragma unroll 1
-        for (int fb = 0; fb < v.m; fb += kFrameBatch) {
-            const int nf = min(kFrameBatch, v.m - fb);
-            lds_barrier();
-            for (int fr = half; fr < nf; fr += 2)
-                sv[arr][fr][col] = live ? src[fbase + (int64_t)(fb + fr) * v.K] : make_float2(0.f, 0.f);
-            lds_barrier();
-#pragma unroll 1
-            for (int fr = 0; fr < nf; ++fr) {
-                float2 a[2], b[2], cc[2], d[2], E[2], F[2];
+        for (int j = 0; j < kSlots; ++j) sv[buf][arr][half + 2 * j][col] = pre[j];
+        lds_barrier();
+        buf ^= 1;
+        if (last) {
+            ++c;
+            fb = 0;
+        } else {
+            fb += kS4FFrames;
+        }
+        if (b + 1 < n_batches) fetch(c, fb);
+
+        if (first) {
+            pacc = make_float2(0.f, 0.f);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    a[u] = sv[0][fr][ti + 16 * u];
-                    b[u] = sv[1][fr][ti + 16 * u];
-                    cc[u] = sv[2][fr][tj + 16 * u];
-                    d[u] = sv[3][fr][tj + 16 * u];
-                    E[u] = make_float2(fmaf(a[u].x, b[u].x, a[u].y * b[u].y), fmaf(a[u].y, b[u].x, -(a[u].x * b[u].y)));
-                    F[u] = make_float2(fmaf(cc[u].x, d[u].x, cc[u].y * d[u].y), fmaf(cc[u].y, d[u].x, -(cc[u].x * d[u].y)));
-                    e[u].x += E[u].x;
-                    e[u].y += E[u].y;
-                    f[u].x += F[u].x;
-                    f[u].y += F[u].y;
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) {
-                        const int q = u * 2 + w;
-                        cmac(sef[q], E[u], F[w]);
-                        cmac(gac[q], a[u], cc[w]);
-                        cmac(gbd[q], b[u], d[w]);
-                        cmacc(had[q], a[u], d[w]);
-                        cmacc(hbc[q], b[u], cc[w]);
-                    }
-            }
+            for (int q = 0; q < 10; ++q) d[q] = floatx4_t{};
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int s = 0; s < kSlots; ++s) {
+            if (2 * s >= nf) break;
+            const int f = 2 * s + (g >> 1);
+            const float2 a = sb[0][f][rowA], bb = sb[1][f][rowA], cc = sb[2][f][rowB], dd = sb[3][f][rowB];
+            float2 E = make_float2(fmaf(a.x, bb.x, a.y * bb.y), fmaf(a.y, bb.x, -(a.x * bb.y)));
+            float2 F = make_float2(fmaf(cc.x, dd.x, cc.y * dd.y), fmaf(cc.y, dd.x, -(cc.x * dd.y)));
+            // k side: Im then Re (1; negated first step: n), -Re then Im (2)
+            const float E1 = second ? E.x : E.y, a1 = second ? a.x : a.y, b1 = second ? bb.x : bb.y;
+            const float En = flip(E1, neg_first), an = flip(a1, neg_first), bn = flip(b1, neg_first);
+            const float a2 = flip(second ? a.y : a.x, neg_first), b2 = flip(second ? bb.y : bb.x, neg_first);
+            // l side: Im then Re (1), Re then Im (2)
+            const float F1 = second ? F.x : F.y, F2 = second ? F.y : F.x;
+            const float c1_ = second ? cc.x : cc.y, c2_ = second ? cc.y : cc.x;
+            const float d1 = second ? dd.x : dd.y, d2 = second ? dd.y : dd.x;
+            d[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(En, F1, d[0], 0, 0, 0);       // E F
+            d[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(E1, F2, d[1], 0, 0, 0);
+            d[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(an, c1_, d[2], 0, 0, 0);      // a c
+            d[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, c2_, d[3], 0, 0, 0);
+            d[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(bn, d1, d[4], 0, 0, 0);       // b d
+            d[5] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, d2, d[5], 0, 0, 0);
+            d[6] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, d1, d[6], 0, 0, 0);       // a d*
+            d[7] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2, d1, d[7], 0, 0, 0);
+            d[8] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, c1_, d[8], 0, 0, 0);      // b c*
+            d[9] = __builtin_amdgcn_mfma_f32_16x16x4f32(b2, c1_, d[9], 0, 0, 0);
+            swap_halves(E.x, F.x);
+            swap_halves(E.y, F.y);
+            pacc.x += E.x;
+            pacc.x += F.x;
+            pacc.y += E.y;
+            pacc.y += F.y;
+        }
+        if (!last) continue;
+
+        wave_lds_fence();
+        if (!second) ps[w][g >> 1][li] = pacc;          // g = 0: e of row li, g = 2: f of column li
+        wave_lds_fence();
+        const float2 f32 = ps[w][1][li];
+        const double fr_ = f32.x, fi = f32.y;
 #pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                const int q = u * 2 + w;
-                // T = e f + G_ac conj(G_bd) + H_ad conj(H_bc), in FP64
-                const double er = e[u].x, ei = e[u].y, fr_ = f[w].x, fi = f[w].y;
-                double tr = er * fr_ - ei * fi, tim = er * fi + ei * fr_;
-                const double g1r = gac[q].x, g1i = gac[q].y, g2r = gbd[q].x, g2i = gbd[q].y;
-                tr += g1r * g2r + g1i * g2i;
-                tim += g1i * g2r - g1r * g2i;
-                const double h1r = had[q].x, h1i = had[q].y, h2r = hbc[q].x, h2i = hbc[q].y;
-                tr += h1r * h2r + h1i * h2i;
-                tim += h1i * h2r - h1r * h2i;
-                const double vr = fma(-gamma, tr, (double)sef[q].x);
-                const double vi = fma(-gamma, tim, (double)sef[q].y);
-                acc[q][0] += vr;
-                acc[q][1] += vi;
-                acc[q][2] = fma(vr, vr, acc[q][2]);
-                acc[q][3] = fma(vi, vi, acc[q][3]);
-            }
+        for (int q = 0; q < 4; ++q) {
+            // T = e f + G_ac conj(G_bd) + H_ad conj(H_bc), in FP64
+            const float2 e32 = ps[w][0][4 * g + q];
+            const double er = e32.x, ei = e32.y;
+            double tr = fma(er, fr_, -(ei * fi)), tim = fma(er, fi, ei * fr_);
+            const double g1r = d[2][q], g1i = d[3][q], g2r = d[4][q], g2i = d[5][q];
+            tr = fma(g1r, g2r, fma(g1i, g2i, tr));
+            tim = fma(g1i, g2r, fma(-g1r, g2i, tim));
+            const double h1r = d[6][q], h1i = d[7][q], h2r = d[8][q], h2i = d[9][q];
+            tr = fma(h1r, h2r, fma(h1i, h2i, tr));
+            tim = fma(h1i, h2r, fma(-h1r, h2i, tim));
+            const double vr = fma(-gamma, tr, (double)d[0][q]);
+            const double vi = fma(-gamma, tim, (double)d[1][q]);
+            acc[q][0] += vr;
+            acc[q][1] += vi;
+            acc[q][2] = fma(vr, vr, acc[q][2]);
+            acc[q][3] = fma(vi, vi, acc[q][3]);
+        }
     }
 
     constexpr int TT = kTileX * kTileX;
     double* o = it.part;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int q = 0; q < 4; ++q) {
+        const int idx = (16 * (w >> 1) + 4 * g + q) * kTileX + rowB;
 #pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            const int idx = (ti + 16 * u) * kTileX + tj + 16 * w;
-#pragma unroll
-            for (int comp = 0; comp < 4; ++comp) {
-                double val = acc[u * 2 + w][comp];
-                if (p.accumulate) val += o[comp * TT + idx];
-                o[comp * TT + idx] = val;
-            }
+        for (int comp = 0; comp < 4; ++comp) {
+            double val = acc[q][comp];
+            if (p.accumulate) val += o[comp * TT + idx];
+            o[comp * TT + idx] = val;
         }
+    }
     }
 }
 
 // ------------------------------------------------------------------ S4, channel combinations, matrix cores
-// The sums of k_s4_cross on the matrix cores (v_mfma_f32_16x16x32_bf16, FP32
+// The sums of k_s4_cross_f32 on the matrix cores (v_mfma_f32_16x16x32_bf16, FP32
 // accumulation, the BF16 x 3 split and 6-slot frame layout of k_s4_mfma_bf16).
 // Each complex frame sum is four real Gram contractions, e.g.
 //   sum E_k F_l = (sum E_r F_r - sum E_i F_i) + j (sum E_r F_i + sum E_i F_r),
@@ -1603,7 +1702,10 @@ hipError_t launch_s3(const BatchArgs& a, hipStream_t s) {
 
 hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
-    k_s4_single<<<item_grid(a), kS4Threads, 0, s>>>(a);
+    if (a.m <= kS4FFrames)
+        k_s4_mfma_f32<true><<<item_grid(a), kS4Threads, 0, s>>>(a);
+    else
+        k_s4_mfma_f32<false><<<item_grid(a), kS4Threads, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -1631,18 +1733,20 @@ int s4_cross_mfma_blocks_per_cu() {
 
 hipError_t launch_s4_cross(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
-    k_s4_cross<<<item_grid(a), kS4XThreads, 0, s>>>(a);
+    k_s4_cross_f32<<<item_grid(a), kS4XThreads, 0, s>>>(a);
     return hipGetLastError();
 }
 
 int s4_cross_blocks_per_cu() {
-    return blocks_per_cu(reinterpret_cast<const void*>(&k_s4_cross), kS4XThreads);
+    return blocks_per_cu(reinterpret_cast<const void*>(&k_s4_cross_f32), kS4XThreads);
 }
 
 int s3_blocks_per_cu() {
     return blocks_per_cu(reinterpret_cast<const void*>(&k_s3<kFrameBatch>), kS3Threads);
 }
-int s4_blocks_per_cu() { return blocks_per_cu(reinterpret_cast<const void*>(&k_s4_single), kS4Threads); }
+int s4_blocks_per_cu() {
+    return blocks_per_cu(reinterpret_cast<const void*>(&k_s4_mfma_f32<false>), kS4Threads);
+}
 hipError_t launch_s4_mfma_f16(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
     if (a.op4) {
