@@ -188,6 +188,40 @@ struct ps_plan_s {
         const int8_t* q = &c4[4 * i];
         return s4_shift == 0 && q[0] == q[2] && q[1] == q[3];
     }
+    // Combination (a, b, d, c) that the matrix-core cross-channel kernel forms
+    // together with combination i = (a, b, c, d) (same Grams), or -1; for the
+    // second of a pair, `first` is set and the index is the first's.
+    int s4_pair(int i, bool& first) const {
+        const int8_t* q = &c4[4 * i];
+        first = true;
+        if (precision != PS_PREC_BF16X3 || s4_shift != 0 || q[0] == q[1] || q[2] == q[3] || s4_sym(i)) return -1;
+        // the k-th combination (a, b, c, d) goes with the k-th (a, b, d, c)
+        int nth = 0, same = 0;
+        auto is = [&](int j, int c, int d) {
+            const int8_t* r = &c4[4 * j];
+            return r[0] == q[0] && r[1] == q[1] && r[2] == c && r[3] == d;
+        };
+        for (int j = 0; j < i; ++j) nth += is(j, q[2], q[3]);
+        for (int j = 0; j < n4(); ++j)
+            if (is(j, q[3], q[2]) && same++ == nth) {
+                if (s4_sym(j)) return -1;
+                first = i < j;
+                return j;
+            }
+        return -1;
+    }
+    // Relative cost of a unit of combination i in the cross-channel kernels,
+    // in tenths, for the work split: where channels coincide, Grams are shared
+    // (see k_s4_cross_mfma; per chunk 40 matrix instructions and 200 FP64 ones
+    // in the general form, 44 and 310 for a pair, 24 and 160 with a == b or
+    // c == d, 16 and 130 with both).
+    int s4x_cost(int i) const {
+        const int8_t* q = &c4[4 * i];
+        bool first;
+        if (precision != PS_PREC_BF16X3 || s4_shift != 0) return 10;
+        if (s4_pair(i, first) >= 0) return 13;
+        return q[0] == q[1] && q[2] == q[3] ? 6 : q[0] == q[1] || q[2] == q[3] ? 8 : 10;
+    }
     // Frame lengths: fc[0] mirrors the fields above (same device tables);
     // fc[1..] are the further frame lengths records may carry.
     std::vector<FrameClass> fc;
@@ -239,10 +273,12 @@ int64_t units_per_block(const std::vector<int64_t>& U_seg, int64_t slots) {
     for (int64_t k = 1; k <= 64; ++k) consider((U_max + k - 1) / k);
     return best_L;
 }
-int32_t seg_blocks(int64_t T, int64_t Np, int64_t L, bool per_chunk) {
+// Units of a segment whose units cost `tenths` / 10 of the stage's common one.
+int64_t weighted(int64_t units, int tenths) { return (units * tenths + 9) / 10; }
+int32_t seg_blocks(int64_t T, int64_t Np, int64_t L, bool per_chunk, int tenths = 10) {
     if (per_chunk) return (int32_t)T;
     const int64_t U = T * Np;
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(U, (U + L - 1) / L));
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(U, (weighted(U, tenths) + L - 1) / L));
 }
 
 // Window (FP64, its power sums kept), FFT twiddles exp(+2 pi j t / N2)
@@ -512,8 +548,11 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
             for (int i = 0; i < p->n2(); ++i) U2.push_back((int64_t)kblocks * Np);
             for (int i = 0; i < p->n3(); ++i) U3.push_back(fc.n_tiles[p->s3_sym(i) ? ps::kSym64 : ps::kFull64] * Np);
             for (int i = 0; i < p->n4(); ++i) {
+                bool first = true;
                 if (p->s4_single(i)) U4s.push_back(fc.n_tiles[ps::kSym64] * Np);
-                else U4x.push_back(fc.n_tiles[p->s4_sym(i) ? ps::kSym32 : ps::kFull32] * Np);
+                else if (p->s4_pair(i, first) < 0 || first)
+                    U4x.push_back(
+                        weighted(fc.n_tiles[p->s4_sym(i) ? ps::kSym32 : ps::kFull32] * Np, p->s4x_cost(i)));
             }
         }
         const int64_t L2 = units_per_block(U2, 4LL * p->n_cu);
@@ -602,13 +641,16 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 G.s3.add(sg, sg.blocks);
                 finalize(G.f3, fin3, i, sg, (int64_t)sg.n_tiles * (TT / 256));
             }
+            std::vector<int64_t> part4(p->n4());
             for (int i = 0; i < p->n4(); ++i) {
                 ps::Seg sg = base;
                 const bool single = p->s4_single(i), sym = p->s4_sym(i);
+                bool first = true;
+                const int pair = single ? -1 : p->s4_pair(i, first);
                 sg.tiles = single ? ps::kSym64 : (sym ? ps::kSym32 : ps::kFull32);
                 sg.tile_tab = fc.d_tiles[sg.tiles];
                 sg.n_tiles = fc.n_tiles[sg.tiles];
-                sg.blocks = seg_blocks(sg.n_tiles, q.Np, single ? L4s : L4x, per_chunk);
+                sg.blocks = seg_blocks(sg.n_tiles, q.Np, single ? L4s : L4x, per_chunk, single ? 10 : p->s4x_cost(i));
                 for (int j = 0; j < 4; ++j) sg.ch[j] = p->c4[4 * i + j];
                 sg.ncomp = single ? 2 : 4;
                 if (single && k.op_chunks > 0) {
@@ -619,13 +661,27 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                     sg.p4 = (int64_t)(k.p4_off / sizeof(double)) + (per_chunk ? 0 : q.chunk0c * 2 * ngp);
                     sg.p4_cs = k.op_chunks * 2 * ngp;
                 }
-                sg.part = part;
-                part += ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * sg.ncomp * (single ? TT : TX);
+                // (a pair's two combinations have the same tiles and blocks)
+                const int64_t n_part = ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * sg.ncomp * (single ? TT : TX);
+                if (first) {
+                    sg.part = part4[i] = part;
+                    part += n_part;
+                    if (pair >= 0) {
+                        part4[pair] = part;
+                        part += n_part;
+                    }
+                } else {
+                    sg.part = part4[i];
+                }
                 sg.out = o && o->d_s4 ? o->d_s4 + 2 * i * nf2 : nullptr;
                 sg.err = o && o->d_s4_err ? o->d_s4_err + 2 * i * nf2 : nullptr;
                 sg.scale = scl.s4;
                 sg.sym = sym;
-                (single ? G.s4s : G.s4x).add(sg, sg.blocks);
+                if (first) {
+                    ps::Seg ms = sg;
+                    if (pair >= 0) ms.part2 = part4[pair];
+                    (single ? G.s4s : G.s4x).add(ms, ms.blocks);
+                }
                 finalize(G.f4, fin4, i, sg, (int64_t)sg.n_tiles * ((single ? TT : TX) / 256));
             }
         }

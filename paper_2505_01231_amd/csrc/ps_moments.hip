@@ -1463,59 +1463,120 @@ __global__ __launch_bounds__(kS4XThreads, 3) void k_s4_cross_f32(BatchArgs p) {
 // row types (Re, Im of E = a' b'*, a', b') and six l-side types (F = c' d'*,
 // c', d').  Tiles are 32 x 32; wave w owns the 16 x 16 block
 // (16 (w / 2), 16 (w % 2)) with 20 accumulators of 4 registers, lane (lg, li)
-// holding grid points (4 lg + e, li).  LDS rows are 160 bytes apart, a stride
-// at which the 16-row, 16-byte-per-lane operand reads of 16x16x32 are free of
-// bank conflicts.  As in k_s4_mfma_bf16 the Grams leave the matrix cores as
+// holding grid points (4 lg + e, li).  An LDS row is 128 bytes (30 words of
+// operands and two of zeros), its eight 16-byte pieces permuted by the row
+// (op_word), so that 16 rows' pieces of one index lie in different banks.  As in k_s4_mfma_bf16 the Grams leave the matrix cores as
 // FP32 and everything after them is FP64: the complex frame sums are
 // assembled from the real Grams, and the k-statistic combination
 //   v = sum E F - gamma T,  T = e f + G_ac conj(G_bd) + H_ad conj(H_bc),
 // gamma = (m-1)/(m(m+1)), is formed in double before the FP64 chunk sums.
-constexpr int kOpDwX = 40;           // 32-bit words per LDS operand row (160 B; 32 used)
+constexpr int kOpDwX = 32;           // 32-bit words per LDS operand row
 constexpr int kS4XMThreads = 256;
 constexpr int kCrossSlots = 3;       // frame slots q, q + 4, q + 8 of a loader thread
 
+// Grams that are the same are formed once, every sum as the general form has
+// it, bit for bit:
+//   a == b: those of b are those of a (12 Grams, four k-side row types),
+//   c == d: likewise on the l side,
+//   both:   8 Grams;
+//   pair:   (a, b, c, d) and (a, b, d, c), a != b, c != d, share the products
+//           of the channel pairs ac, bc, bd, ad and both of Re F = Re F'
+//           (F' = d' c'*); Im F' = -Im F up to its rounding, a seventh l-side
+//           row type: 22 Grams for two combinations.
+// What bounds it: two waves per SIMD (80 to 88 Gram registers, 32 to 64 of
+// FP64 sums) run staging, matrix and FP64 phases one after another between two
+// barriers; timing builds without staging, without the Grams or without the
+// combination save about as much as each takes alone, so work that is not done
+// counts whatever unit it is for.  Three waves per SIMD (168 registers) spill
+// in the chunk loop and take 30.9 ms.  Measured (four channels, every orbit of
+// S4, five records of 4.4e6 samples in all, N_f = 256, m = 10): 15.1 ms, every
+// combination in the general form 19.0.
+enum CrossForm { kXGeneral, kXPair, kXSameAB, kXSameCD, kXSameBoth };
+
+// 32-bit word `word` of an LDS operand row.
+__device__ __forceinline__ int op_word(int row, int word) {
+    return row * kOpDwX + (((word >> 2) ^ ((row >> 1) & 7)) << 2) + (word & 3);
+}
+
 // Stage this thread's frame slots of column `col`: P = x conj(y) and the split
-// words of (Re P, Im P, Re x, Im x, Re y, Im y) into row types 0..5; returns
-// the sum of P over the slots.
-template <int SIDE>
-__device__ __forceinline__ float2 stage_cross(uint32_t (*op)[kOpDwX], int col, int q, const float2 (&px)[kCrossSlots],
-                                              const float2 (&py)[kCrossSlots]) {
-    float2 pa = make_float2(0.f, 0.f);
+// words of NT of (Re P, Im P, Re x, Im x, Re y, Im y, Im y conj(x)) into row
+// types 0..; adds the slots' P and Im y conj(x) to pa and pb.
+template <int SIDE, bool SAME, int NT>
+__device__ __forceinline__ void stage_cross(uint32_t* op, int col, int q, const float2 (&px)[kCrossSlots],
+                                            const float2 (&py)[kCrossSlots], float2& pa, float& pb) {
+    float2 sum = make_float2(0.f, 0.f);
+    float sum_b = 0.f;
 #pragma unroll
     for (int j = 0; j < kCrossSlots; ++j) {
         const int f = q + 4 * j;
         if (f >= kMfmaFrames) break;
-        const float2 x = px[j], y = py[j];
+        const float2 x = px[j], y = SAME ? x : py[j];
         const float2 P = make_float2(fmaf(x.x, y.x, x.y * y.y), fmaf(x.y, y.x, -(x.x * y.y)));
-        pa.x += P.x;
-        pa.y += P.y;
-        const float val[6] = {P.x, P.y, x.x, x.y, y.x, y.y};
+        const float Pb = NT > 6 ? fmaf(y.y, x.x, -(y.x * x.y)) : 0.f;
+        sum.x += P.x;
+        sum.y += P.y;
+        sum_b += Pb;
+        const float val[7] = {P.x, P.y, x.x, x.y, y.x, y.y, Pb};
+        uint32_t* wr[3];
 #pragma unroll
-        for (int t = 0; t < 6; ++t) {
-            uint32_t w0, w1, w2;
-            split_words<SIDE>(val[t], w0, w1, w2);
-            uint32_t* wr = &op[t * kTileX + col][3 * f];
-            wr[0] = w0;
-            wr[1] = w1;
-            wr[2] = w2;
+        for (int i = 0; i < 3; ++i) wr[i] = op + op_word(col, 3 * f + i);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            uint32_t w[3];
+            split_words<SIDE>(val[t], w[0], w[1], w[2]);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) wr[i][t * kTileX * kOpDwX] = w[i];
         }
     }
-    return pa;
+    pa.x += sum.x;
+    pa.y += sum.y;
+    pb += sum_b;
 }
 
-// ONE_BATCH: every chunk fits one frame batch (m <= 10), so each batch starts
-// and ends a chunk (compile-time).
-template <bool ONE_BATCH>
-__global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) {
-    __shared__ __attribute__((aligned(16))) uint32_t opA[6 * kTileX][kOpDwX];
-    __shared__ __attribute__((aligned(16))) uint32_t opB[6 * kTileX][kOpDwX];
-    __shared__ float2 psum[2][kTileX];
+constexpr int kXRows = 13 * kTileX, kXRowsA = 6 * kTileX;
 
-    Block bk;
-    View v;
-    if (!resolve_block(p, bk, v)) return;
+struct CrossLds {
+    __attribute__((aligned(16))) uint32_t op[kXRows * kOpDwX];      // six k-side row types, seven l-side ones
+    float2 psum[2][kTileX];
+    float psum_b[kTileX];
+};
 
-    const int tid = threadIdx.x;
+// The combination: v = sum E F - gamma T, T = e f + G1 conj(G2) + H1 conj(H2),
+// from the sums of E F (x), G and H in FP64, added to the point's chunk sums.
+struct Cplx {
+    double r, i;
+};
+__device__ __forceinline__ void cross_combine(double (&acc)[4], double gamma, Cplx x, Cplx e, Cplx f, Cplx g1, Cplx g2,
+                                              Cplx h1, Cplx h2) {
+    double tr = fma(e.r, f.r, -(e.i * f.i));
+    double ti = fma(e.r, f.i, e.i * f.r);
+    tr = fma(g1.r, g2.r, fma(g1.i, g2.i, tr));
+    ti = fma(g1.i, g2.r, fma(-g1.r, g2.i, ti));
+    tr = fma(h1.r, h2.r, fma(h1.i, h2.i, tr));
+    ti = fma(h1.i, h2.r, fma(-h1.r, h2.i, ti));
+    const double vr = fma(-gamma, tr, x.r);
+    const double vi = fma(-gamma, ti, x.i);
+    acc[0] += vr;
+    acc[1] += vi;
+    acc[2] = fma(vr, vr, acc[2]);
+    acc[3] = fma(vi, vi, acc[3]);
+}
+
+// One piece of work.  ONE_BATCH: every chunk fits one frame batch (m <= 10), so
+// each batch starts and ends a chunk (compile-time).
+template <int FORM, bool ONE_BATCH>
+__device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v, const Item& it, double* part_pair,
+                                              CrossLds& sm) {
+    constexpr bool kAB = FORM == kXSameAB || FORM == kXSameBoth, kCD = FORM == kXSameCD || FORM == kXSameBoth;
+    constexpr bool kPair = FORM == kXPair;
+    constexpr int kOut = kPair ? 2 : 1;
+    constexpr int kPairs = (kAB ? 1 : 2) * (kCD ? 1 : 2);       // channel pairs
+    constexpr int kGrams = 4 + 4 * kPairs + (kPair ? 2 : 0);
+
+    int tid = threadIdx.x;
+    // Nothing of this form's set-up is kept across pieces of work: the five
+    // forms' addresses together would spill.
+    asm volatile("" : "+v"(tid));
     const int lane = tid & 63, w = tid >> 6;
     const int li = lane & 15, lg = lane >> 4;
     const int rowA = 16 * (w >> 1) + li, rowB = 16 * (w & 1) + li;
@@ -1527,17 +1588,9 @@ __global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) 
     const int side = __builtin_amdgcn_readfirstlane(tid >> 7);    // uniform per wave
     const int col = 16 * (w & 1) + (((lane >> 2) & 3) | (((lane >> 5) & 1) << 2) | (((lane >> 4) & 1) << 3));
     const int q = tid & 3;
-    uint32_t(*op)[kOpDwX] = side ? opB : opA;
-
-    for (int r = tid; r < 2 * 6 * kTileX; r += kS4XMThreads) {
-        uint32_t* row = (r < 6 * kTileX) ? opA[r] : opB[r - 6 * kTileX];
-        row[3 * kMfmaFrames] = 0u;
-        row[3 * kMfmaFrames + 1] = 0u;
-    }
+    uint32_t* op = sm.op + (side ? kXRowsA * kOpDwX : 0);
     const double gamma = p.gamma;                       // (m-1)/(m(m+1)) (natural: 1/m)
 
-    Item it;
-    while (next_item<kTileX, 4>(p, bk, it)) {
     const int c0 = it.c0, c1 = it.c1;
     const int gcol = (side ? it.l0 : it.k0) + col;
     const bool live = gcol < v.Nf;
@@ -1546,117 +1599,168 @@ __global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) 
     const float2* srcx = v.coef + it.ch[2 * side] * v.cs + gcol + shx;        // a (k side) or c (l side)
     const float2* srcy = v.coef + it.ch[2 * side + 1] * v.cs + gcol - shx;    // b or d
 
-    double acc[4][4];
+    double acc[kOut][4][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e][0] = acc[e][1] = acc[e][2] = acc[e][3] = 0.0;
+    for (int e = 0; e < 4 * kOut; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[e >> 2][e & 3][i] = 0.0;
 
     constexpr int kJ = kCrossSlots;
-    const int per_chunk = (v.m + kMfmaFrames - 1) / kMfmaFrames;
+    const int per_chunk = ONE_BATCH ? 1 : (v.m + kMfmaFrames - 1) / kMfmaFrames;
     const int n_batches = (c1 - c0) * per_chunk;
     float2 px[kJ], py[kJ];
-    auto fetch = [&](int b) {
-        const int c = c0 + b / per_chunk;
-        const int fb = (b % per_chunk) * kMfmaFrames;
+    auto fetch = [&](int c, int fb) {
         const int nf = min(kMfmaFrames, v.m - fb);
         const int64_t o = v.off + ((int64_t)c * v.m + fb) * v.K;
+        const bool same = side ? kCD : kAB;
 #pragma unroll
         for (int j = 0; j < kJ; ++j) {
             const int f = q + 4 * j;
             const bool ok = live && f < nf;
             px[j] = ok ? srcx[o + (int64_t)f * v.K] : make_float2(0.f, 0.f);
-            py[j] = ok ? srcy[o + (int64_t)f * v.K] : make_float2(0.f, 0.f);
+            if (!same) py[j] = ok ? srcy[o + (int64_t)f * v.K] : make_float2(0.f, 0.f);
         }
     };
-    if (n_batches > 0) fetch(0);
+    if (n_batches > 0) fetch(c0, 0);
 
-    floatx4_t d[20];
+    floatx4_t d[kGrams];
     float2 pacc = make_float2(0.f, 0.f);
+    float pacc_b = 0.f;
+    int c = c0, fb = 0;                                 // chunk and first frame of the batch
 #pragma unroll 1
     for (int b = 0; b < n_batches; ++b) {
-        const int fbi = ONE_BATCH ? 0 : b % per_chunk;
-        const bool first = ONE_BATCH || fbi == 0, last = ONE_BATCH || fbi == per_chunk - 1;
-        if (first) pacc = make_float2(0.f, 0.f);
-        lds_barrier();
-        {   // E = x conj(y) (k side: a b*, l side: c d*)
-            const float2 pa = side == 0 ? stage_cross<0>(op, col, q, px, py) : stage_cross<1>(op, col, q, px, py);
-            pacc.x += pa.x;
-            pacc.y += pa.y;
+        const bool first = ONE_BATCH || fb == 0, last = ONE_BATCH || fb + kMfmaFrames >= v.m;
+        if (first) {
+            pacc = make_float2(0.f, 0.f);
+            pacc_b = 0.f;
         }
+        lds_barrier();
+        // E = x conj(y) (k side: a b*, l side: c d*)
+        if (side == 0) stage_cross<0, kAB, kAB ? 4 : 6>(op, col, q, px, py, pacc, pacc_b);
+        else stage_cross<1, kCD, kCD ? 4 : kPair ? 7 : 6>(op, col, q, px, py, pacc, pacc_b);
         if (last) {
             float2 tot = pacc;
             tot.x += xor1(tot.x);
             tot.y += xor1(tot.y);
             tot.x += __shfl_xor(tot.x, 2);
             tot.y += __shfl_xor(tot.y, 2);
-            if (q == 0) psum[side][col] = tot;
+            if (q == 0) sm.psum[side][col] = tot;
+            if (kPair && side) {
+                float tot_b = pacc_b;
+                tot_b += xor1(tot_b);
+                tot_b += __shfl_xor(tot_b, 2);
+                if (q == 0) sm.psum_b[col] = tot_b;
+            }
         }
+        if (last) {
+            ++c;
+            fb = 0;
+        } else {
+            fb += kMfmaFrames;
+        }
+        if (b + 1 < n_batches) fetch(c, fb);
         lds_barrier();
-        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            const int wo = 16 * ks + 4 * lg;
-            bf16x8_t A[6], B[6];
-#pragma unroll
-            for (int t = 0; t < 6; ++t) {
-                A[t] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&opA[t * kTileX + rowA][wo]));
-                B[t] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&opB[t * kTileX + rowB][wo]));
+            const uint32_t* oa = sm.op + op_word(rowA, 16 * ks + 4 * lg);
+            const uint32_t* ob = sm.op + kXRowsA * kOpDwX + op_word(rowB, 16 * ks + 4 * lg);
+            auto A = [&](int t) { return *reinterpret_cast<const u32x4_t*>(oa + t * kTileX * kOpDwX); };
+            auto B = [&](int t) { return *reinterpret_cast<const u32x4_t*>(ob + t * kTileX * kOpDwX); };
+            auto gram = [&](int i, u32x4_t x, u32x4_t y) {
+                const floatx4_t z = {0.f, 0.f, 0.f, 0.f};
+                d[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x),
+                                                               __builtin_bit_cast(bf16x8_t, y),
+                                                               (first && ks == 0) ? z : d[i], 0, 0, 0);
+            };
+            // Grams rr, ii, ri, ir of (re, im) operand pairs
+            auto grams = [&](int g, u32x4_t xr, u32x4_t xi, u32x4_t yr, u32x4_t yi) {
+                gram(g, xr, yr), gram(g + 1, xi, yi), gram(g + 2, xr, yi), gram(g + 3, xi, yr);
+            };
+            {
+                const u32x4_t er = A(0), ei = A(1);
+                grams(0, er, ei, B(0), B(1));               // E F
+                if constexpr (kPair) {
+                    const u32x4_t fb = B(6);
+                    gram(20, ei, fb), gram(21, er, fb);     // ii, ri of E F'
+                }
             }
-            // (A type, B type) of the 20 Grams: E.F, a.c, b.c, b.d, a.d, each rr, ii, ri, ir
-            constexpr int ga[20] = {0, 1, 0, 1, 2, 3, 2, 3, 4, 5, 4, 5, 4, 5, 4, 5, 2, 3, 2, 3};
-            constexpr int gb[20] = {0, 1, 1, 0, 2, 3, 3, 2, 2, 3, 3, 2, 4, 5, 5, 4, 4, 5, 5, 4};
-            const floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int g = 0; g < 20; ++g)
-                d[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[ga[g]], B[gb[g]], (first && ks == 0) ? z : d[g], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            const u32x4_t ar = A(2), ai = A(3), cr = B(2), ci = B(3);
+            grams(4, ar, ai, cr, ci);                       // ac
+            if constexpr (!kCD) {
+                const u32x4_t dr = B(4), di = B(5);
+                grams(8, ar, ai, dr, di);                   // ad
+                if constexpr (!kAB) {
+                    const u32x4_t br = A(4), bi = A(5);
+                    grams(12, br, bi, cr, ci);              // bc
+                    grams(16, br, bi, dr, di);              // bd
+                }
+            } else if constexpr (!kAB) {
+                grams(8, A(4), A(5), cr, ci);               // bc
+            }
         }
-        __builtin_amdgcn_s_setprio(0);
-        if (b + 1 < n_batches) fetch(b + 1);
         if (!last) continue;
 
-        const float2 fl32 = psum[1][rowB];
-        const double flr = fl32.x, fli = fl32.y;
+        const float2 fl32 = sm.psum[1][rowB];
+        const Cplx fl = {fl32.x, fl32.y};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float2 ek = psum[0][16 * (w >> 1) + 4 * lg + e];
-            double g[20];
-#pragma unroll
-            for (int i = 0; i < 20; ++i) g[i] = d[i][e];
-            // complex frame sums from the real Grams, in FP64
-            const double sef_r = g[0] - g[1], sef_i = g[2] + g[3];
-            const double gac_r = g[4] - g[5], gac_i = g[6] + g[7];
-            const double hbc_r = g[8] + g[9], hbc_i = g[11] - g[10];
-            const double gbd_r = g[12] - g[13], gbd_i = g[14] + g[15];
-            const double had_r = g[16] + g[17], had_i = g[19] - g[18];
-            // T = e f + G_ac conj(G_bd) + H_ad conj(H_bc)
-            const double ekr = ek.x, eki = ek.y;
-            double tr = fma(ekr, flr, -(eki * fli));
-            double ti = fma(ekr, fli, eki * flr);
-            tr = fma(gac_r, gbd_r, fma(gac_i, gbd_i, tr));
-            ti = fma(gac_i, gbd_r, fma(-gac_r, gbd_i, ti));
-            tr = fma(had_r, hbc_r, fma(had_i, hbc_i, tr));
-            ti = fma(had_i, hbc_r, fma(-had_r, hbc_i, ti));
-            const double vr = fma(-gamma, tr, sef_r);
-            const double vi = fma(-gamma, ti, sef_i);
-            acc[e][0] += vr;
-            acc[e][1] += vi;
-            acc[e][2] = fma(vr, vr, acc[e][2]);
-            acc[e][3] = fma(vi, vi, acc[e][3]);
+            const float2 ek32 = sm.psum[0][16 * (w >> 1) + 4 * lg + e];
+            // complex frame sums from the real Grams, in FP64: of x y, of x y*
+            auto G = [&](int o) {
+                return Cplx{(double)d[o][e] - (double)d[o + 1][e], (double)d[o + 2][e] + (double)d[o + 3][e]};
+            };
+            auto H = [&](int o) {
+                return Cplx{(double)d[o][e] + (double)d[o + 1][e], (double)d[o + 3][e] - (double)d[o + 2][e]};
+            };
+            constexpr int ac = 4, ad = kCD ? 4 : 8, bc = kAB ? 4 : kCD ? 8 : 12, bd = kAB ? ad : kCD ? 8 : 16;
+            const Cplx ek = {ek32.x, ek32.y};
+            cross_combine(acc[0][e], gamma, G(0), ek, fl, G(ac), G(bd), H(ad), H(bc));
+            if constexpr (kPair) {              // c and d exchanged
+                const Cplx x = {(double)d[0][e] - (double)d[20][e], (double)d[21][e] + (double)d[3][e]};
+                cross_combine(acc[1][e], gamma, x, ek, Cplx{fl.r, sm.psum_b[rowB]}, G(ad), G(bc), H(ac), H(bd));
+            }
         }
     }
 
     constexpr int TT = kTileX * kTileX;
-    double* o = it.part;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int idx = (16 * (w >> 1) + 4 * lg + e) * kTileX + rowB;
+    for (int out = 0; out < kOut; ++out) {
+        double* o = out ? part_pair : it.part;
 #pragma unroll
-        for (int comp = 0; comp < 4; ++comp) {
-            double val = acc[e][comp];
-            if (p.accumulate) val += o[comp * TT + idx];
-            o[comp * TT + idx] = val;
+        for (int e = 0; e < 4; ++e) {
+            const int idx = (16 * (w >> 1) + 4 * lg + e) * kTileX + rowB;
+#pragma unroll
+            for (int comp = 0; comp < 4; ++comp) {
+                double val = acc[out][e][comp];
+                if (p.accumulate) val += o[comp * TT + idx];
+                o[comp * TT + idx] = val;
+            }
         }
     }
+}
+
+template <bool ONE_BATCH>
+__global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) {
+    __shared__ CrossLds sm;
+
+    Block bk;
+    View v;
+    if (!resolve_block(p, bk, v)) return;
+    // the operand words past the last frame stay zero
+    for (int r = threadIdx.x; r < kXRows; r += kS4XMThreads) {
+        sm.op[op_word(r, 3 * kMfmaFrames)] = 0u;
+        sm.op[op_word(r, 3 * kMfmaFrames + 1)] = 0u;
+    }
+    // (a plane's factors sit at different columns)
+    const bool ab = p.s4_shift == 0 && bk.s->ch[0] == bk.s->ch[1], cd = p.s4_shift == 0 && bk.s->ch[2] == bk.s->ch[3];
+    const int64_t pair = bk.s->part2 ? bk.s->part2 - bk.s->part : 0;
+    Item it;
+    while (next_item<kTileX, 4>(p, bk, it)) {
+        if (pair) s4_cross_item<kXPair, ONE_BATCH>(p, v, it, it.part + pair, sm);
+        else if (ab && cd) s4_cross_item<kXSameBoth, ONE_BATCH>(p, v, it, nullptr, sm);
+        else if (ab) s4_cross_item<kXSameAB, ONE_BATCH>(p, v, it, nullptr, sm);
+        else if (cd) s4_cross_item<kXSameCD, ONE_BATCH>(p, v, it, nullptr, sm);
+        else s4_cross_item<kXGeneral, ONE_BATCH>(p, v, it, nullptr, sm);
     }
 }
 
