@@ -1332,15 +1332,8 @@ ps::BatchArgs batch_args(const ps_plan_s* p, const Batch& B, const SegTable& t, 
     return a;
 }
 
-ps::FinalizeArgs fin_args(const ps_plan_s* p, const Batch& B, const SegTable& t, char* ws, const char* tab) {
-    ps::FinalizeArgs f{};
-    f.segs = reinterpret_cast<const ps::Seg*>(tab + t.dev_off);
-    f.n_segs = (int)t.v.size();
-    f.n_items = t.n_items;
-    f.part = reinterpret_cast<const double*>(ws + B.off_part);
-    f.s1 = p->has(1) ? reinterpret_cast<const float2*>(ws + B.off_s1) : nullptr;
-    f.s1_cs = B.chunks_tot;
-    return f;
+ps::FinalizeTable fin_table(const SegTable& t, const char* tab) {
+    return {reinterpret_cast<const ps::Seg*>(tab + t.dev_off), (int)t.v.size(), t.n_items};
 }
 
 // The moment stages of one group (one launch each).
@@ -1383,10 +1376,15 @@ ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, 
 
 ps_status launch_finalize(ps_plan_t p, const Batch& B, const Group& G, char* ws, const char* tab, hipStream_t st) {
     StageTimer t(p, st, 5);
-    if (G.f2.n_items) PS_HIP(ps::launch_finalize_vec(fin_args(p, B, G.f2, ws, tab), st));
-    if (G.f3.n_items) PS_HIP(ps::launch_finalize_grid(fin_args(p, B, G.f3, ws, tab), st));
-    if (G.f4.n_items) PS_HIP(ps::launch_finalize_grid(fin_args(p, B, G.f4, ws, tab), st));
-    if (G.f1.n_items) PS_HIP(ps::launch_finalize_s1(fin_args(p, B, G.f1, ws, tab), st));
+    ps::FinalizeArgs f{};
+    f.tab[ps::kFinS1] = fin_table(G.f1, tab);
+    f.tab[ps::kFinS2] = fin_table(G.f2, tab);
+    f.tab[ps::kFinS3] = fin_table(G.f3, tab);
+    f.tab[ps::kFinS4] = fin_table(G.f4, tab);
+    f.part = reinterpret_cast<const double*>(ws + B.off_part);
+    f.s1 = p->has(1) ? reinterpret_cast<const float2*>(ws + B.off_s1) : nullptr;
+    f.s1_cs = B.chunks_tot;
+    PS_HIP(ps::launch_finalize(f, st));
     return PS_OK;
 }
 
@@ -2272,16 +2270,11 @@ ps_status ps_stream_end(ps_accum_t a, const ps_output* out, ps_stream_t stream) 
     ps_status s = upload_tables(p, B, tab, st);
     if (s != PS_OK) return s;
     ps::FinalizeArgs fa{};
+    fa.tab[ps::kFinS2] = fin_table(B.groups[0].f2, tab);
+    fa.tab[ps::kFinS3] = fin_table(B.groups[0].f3, tab);
+    fa.tab[ps::kFinS4] = fin_table(B.groups[0].f4, tab);
     fa.part = a->d_state;
-    auto fin = [&](const SegTable& t, bool vec) -> hipError_t {
-        fa.segs = reinterpret_cast<const ps::Seg*>(tab + t.dev_off);
-        fa.n_segs = (int)t.v.size();
-        fa.n_items = t.n_items;
-        return vec ? ps::launch_finalize_vec(fa, st) : ps::launch_finalize_grid(fa, st);
-    };
-    if (!f2.v.empty()) PS_HIP(fin(B.groups[0].f2, true));
-    if (!f3.v.empty()) PS_HIP(fin(B.groups[0].f3, false));
-    if (!f4.v.empty()) PS_HIP(fin(B.groups[0].f4, false));
+    PS_HIP(ps::launch_finalize(fa, st));
     if (p->has(1))
         PS_HIP(ps::launch_finalize_s1_sums(a->d_state + a->layout.off1, p->C, a->n_chunks, scl.s1, out->d_s1,
                                            out->d_s1_err, st));

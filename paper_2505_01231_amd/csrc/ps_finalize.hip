@@ -42,40 +42,74 @@ __device__ __forceinline__ void combine_sets(double& mean, double& sigma, double
     sigma = 0.5 * (sigma + sigma2);
 }
 
+// Adds `ns` slots to s[0 .. NC): component c of slot i is at
+// q[i stride + c comp + lane] (q uniform over the block).  Slots are added in
+// order, kSlotBatch of them loaded at once; more than two at once measured the
+// same (tiles: bound by the slots' bytes) or lost occupancy.
+constexpr int kSlotBatch = 2;
+
+template <int NC>
+__device__ __forceinline__ void add_slots(double (&s)[4], const double* q, uint32_t lane, int ns, int64_t stride,
+                                          int comp) {
+    for (; ns >= kSlotBatch; ns -= kSlotBatch, q += kSlotBatch * stride) {
+        asm volatile("" : "+v"(lane));      // (scalar base + lane addresses, not a pointer per load kept over the loop)
+        double v[kSlotBatch][NC];
+#pragma unroll
+        for (int u = 0; u < kSlotBatch; ++u)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[u][c] = (q + u * stride + c * comp)[lane];
+#pragma unroll
+        for (int u = 0; u < kSlotBatch; ++u)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s[c] += v[u][c];
+    }
+    if (ns > 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s[c] += (q + c * comp)[lane];
+    }
+}
+
 // S2: one block per (record, combination, 16-wide k group of a 256-wide k
 // block).  Thread (g, kk) adds the slots s0 + g, s0 + g + 16, ... of point kk
 // (of each frame set); the 16 group sums are then added in LDS in group order
 // (a fixed order, so the result does not depend on timing).
 constexpr int kVecGroups = 16;
 
-__global__ __launch_bounds__(256) void k_finalize_vec(FinalizeArgs p) {
-    __shared__ double red[kVecGroups][8][16];
-    const int64_t x = blockIdx.x / kVecGroups;         // item: a 256-wide k block
-    if (x >= p.n_items) return;
-    const int sub = blockIdx.x % kVecGroups;
-    const Seg& sg = p.segs[find_seg(p.segs, p.n_segs, x)];
+struct VecLds {
+    double red[kVecGroups][8][16];
+};
+
+__device__ __forceinline__ void finalize_vec(const FinalizeArgs& p, const FinalizeTable& tab, int64_t block,
+                                             VecLds& sm) {
+    auto& red = sm.red;
+    const int64_t x = block / kVecGroups;              // item: a 256-wide k block
+    const int sub = (int)(block % kVecGroups);
+    ConstSeg& sg = *find_seg(tab.segs, tab.n_segs, x);
     const int64_t t = x - sg.item0;
     const int kk = threadIdx.x & 15, g = threadIdx.x >> 4;
     const int kl = 16 * sub + kk;                       // k within the item
     const int k = (int)t * 256 + kl;
     const bool two = sg.n_chunks2 > 0;
-    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int set = 0; set < (two ? 2 : 1); ++set) {
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+        if (set && !two) break;
         const int64_t W = set ? sg.n_chunks2 : sg.n_chunks;
         int64_t s0 = 0, ns = 0;
         if (W > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, t, s0, ns);
-        const double* part = p.part + (set ? sg.part2 : sg.part) + kl;
-        for (int64_t slot = s0 + g; slot < s0 + ns; slot += kVecGroups) {
-            const double* q = part + slot * 4 * 256;
-            for (int c = 0; c < 4; ++c) s[4 * set + c] += q[c * 256];
-        }
+        double a[4] = {0, 0, 0, 0};
+        add_slots<4>(a, p.part + (set ? sg.part2 : sg.part) + s0 * 4 * 256, (uint32_t)(g * 4 * 256 + kl),
+                     ((int)ns - g + kVecGroups - 1) / kVecGroups, kVecGroups * 4 * 256, 256);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) red[g][4 * set + c][kk] = a[c];
     }
-    const int nc = two ? 8 : 4;                         // uniform over the block
-    for (int c = 0; c < nc; ++c) red[g][c][kk] = s[c];
     __syncthreads();
     if (g != 0 || k >= sg.Nf) return;
-    for (int c = 0; c < nc; ++c) {
+    double s[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
         s[c] = 0;
+        if (c >= 4 && !two) break;
+#pragma unroll 4
         for (int gg = 0; gg < kVecGroups; ++gg) s[c] += red[gg][c][kk];
     }
     double mr, sr, mi, si;
@@ -103,18 +137,22 @@ __global__ __launch_bounds__(256) void k_finalize_vec(FinalizeArgs p) {
 // points (all of them, or only k <= l for symmetric spectra); a symmetric
 // spectrum also gets its mirror (l, k) <- (k, l), k < l, written through an
 // LDS transpose so that both writes are row-contiguous.
-__global__ __launch_bounds__(256) void k_finalize_tiles(FinalizeArgs p) {
-    __shared__ double2 sm[16][17], se[16][17];
-    const int64_t x = blockIdx.x;
-    if (x >= p.n_items) return;
-    const Seg& sg = p.segs[find_seg(p.segs, p.n_segs, x)];
+struct TileLds {
+    double2 mean[16][17], err[16][17];
+};
+
+__device__ __forceinline__ void finalize_tile(const FinalizeArgs& p, const FinalizeTable& tab, int64_t x,
+                                              TileLds& lds) {
+    auto& sm = lds.mean;
+    auto& se = lds.err;
+    ConstSeg& sg = *find_seg(tab.segs, tab.n_segs, x);
     const int E = sg.tiles >= kSym32 ? kTileX : kTile;
     const int TT = E * E;
     const int sub = E / 16, per_tile = sub * sub;
     const int64_t local = x - sg.item0;
     const int tile = (int)(local / per_tile);
     const int sb = (int)(local - (int64_t)tile * per_tile);
-    const int2 t = sg.tile_tab[tile];
+    const int2 t = tile_at(sg.tile_tab, tile);
     const int kb = t.x * E + 16 * (sb / sub), lb = t.y * E + 16 * (sb % sub);   // sub-block origin
     const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
     const int ncomp = sg.ncomp;
@@ -123,25 +161,17 @@ __global__ __launch_bounds__(256) void k_finalize_tiles(FinalizeArgs p) {
     const int k = kb + i, l = lb + j;
     const bool valid = k < sg.Nf && l < sg.Nf && !(sg.sym && k > l);
     double mr = 0.0, sr = 0.0, mi = 0.0, si = 0.0;
-    // The point's offset inside the tile does not depend on the tile table,
-    // and every component of every slot is loaded before any is added (one
-    // round trip to memory, not one per component).
+    // (the point's offset inside the tile does not depend on the tile table)
     const int idx = (16 * (sb / sub) + i) * E + 16 * (sb % sub) + j;
     for (int set = 0; set < (two ? 2 : 1); ++set) {
         const int64_t W = set ? sg.n_chunks2 : sg.n_chunks;
         const double np = (double)W;
         int64_t s0 = 0, ns = 0;
         if (W > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, tile, s0, ns);
-        const double* base = p.part + (set ? sg.part2 : sg.part) + idx;
         double s[4] = {0, 0, 0, 0};
-        for (int64_t slot = s0; slot < s0 + ns; ++slot) {
-            const double* q = base + slot * ncomp * TT;
-            double v[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = c < ncomp ? q[c * TT] : 0.0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) s[c] += v[c];
-        }
+        const double* q = p.part + (set ? sg.part2 : sg.part) + s0 * ncomp * TT;
+        if (ncomp == 4) add_slots<4>(s, q, idx, (int)ns, 4 * TT, TT);
+        else add_slots<2>(s, q, idx, (int)ns, 2 * TT, TT);
         double r_m, r_s, i_m = 0.0, i_s = 0.0;
         if (ncomp == 4) {
             mean_sigma(s[0], s[2], np, sg.scale, r_m, r_s);
@@ -200,23 +230,31 @@ __global__ void k_fill_nan(double* p, int64_t n) {
 // parts and their squares); the partial sums are then added in a fixed tree
 // order.  For a real signal a_0 is real, so Im and sigma_Im come out 0 (NaN
 // where the mean or the error bar is undefined).
-__global__ __launch_bounds__(256) void k_finalize_s1(FinalizeArgs p) {
-    __shared__ double red[8][256];
-    const int64_t x = blockIdx.x;
-    if (x >= p.n_items) return;
-    const Seg& sg = p.segs[find_seg(p.segs, p.n_segs, x)];
+struct S1Lds {
+    double red[8][256];
+};
+
+__device__ __forceinline__ void finalize_s1(const FinalizeArgs& p, const FinalizeTable& tab, int64_t x, S1Lds& sm) {
+    auto& red = sm.red;
+    ConstSeg& sg = *find_seg(tab.segs, tab.n_segs, x);
     const bool two = sg.n_chunks2 > 0;
     const float2* v = p.s1 + (int64_t)sg.ch[0] * p.s1_cs;
     const int tid = threadIdx.x;
     for (int set = 0; set < 2; ++set) {
         const int64_t c0 = set ? sg.part2 : sg.part, W = set ? (two ? sg.n_chunks2 : 0) : sg.n_chunks;
         double sr = 0.0, si = 0.0, sr2 = 0.0, si2 = 0.0;
-        for (int64_t c = tid; c < W; c += 256) {
-            const float2 d = v[c0 + c];
-            sr += d.x;
-            si += d.y;
-            sr2 = fma((double)d.x, (double)d.x, sr2);
-            si2 = fma((double)d.y, (double)d.y, si2);
+        for (int64_t c = tid; c < W; c += 256 * kSlotBatch) {
+            float2 d[kSlotBatch];
+#pragma unroll
+            for (int u = 0; u < kSlotBatch; ++u)
+                d[u] = c + 256 * u < W ? v[c0 + c + 256 * u] : make_float2(0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < kSlotBatch; ++u) {
+                sr += d[u].x;
+                si += d[u].y;
+                sr2 = fma((double)d[u].x, (double)d[u].x, sr2);
+                si2 = fma((double)d[u].y, (double)d[u].y, si2);
+            }
         }
         red[4 * set][tid] = sr;
         red[4 * set + 1][tid] = si;
@@ -250,6 +288,37 @@ __global__ __launch_bounds__(256) void k_finalize_s1(FinalizeArgs p) {
     }
 }
 
+// Every order's finalize in one launch: block ranges of S1, S2, S3 and S4 in
+// this order, so that the few latency-bound blocks of S1 and S2 run beside the
+// tiles.  Bound by the slots' bytes: S3's and S4's 512 slots of 128 and 64 KB
+// are 100 MB, read at 5.5 TB/s (10^6 samples, N = 1024, N_f = 200: 18 us; as
+// launches of their own 15 + 21 + 21 us; 2^26 samples, N = 4096, N_f = 512: 28
+// against 51 + 12 + 12 us, 51200 samples, N_f = 64: 7 against 23 us).
+__global__ __launch_bounds__(256, 8) void k_finalize(FinalizeArgs p) {
+    __shared__ union {
+        VecLds vec;
+        TileLds tile;
+        S1Lds s1;
+    } sm;
+    int64_t x = blockIdx.x;
+    int role = 0;
+    while (role < 3 && x >= p.tab[role].n_blocks) x -= p.tab[role++].n_blocks;
+    const FinalizeTable& tab = p.tab[role];
+    if (role == kFinS1) finalize_s1(p, tab, x, sm.s1);
+    else if (role == kFinS2) finalize_vec(p, tab, x, sm.vec);
+    else finalize_tile(p, tab, x, sm.tile);
+}
+
+// S3 or S4 alone, from kOwnLaunch blocks on: there a launch's 5 us are nothing
+// and the merged kernel's larger LDS and register demand costs 10 % (409
+// records of one chunk, N_f = 256, 65,440 blocks: 446 us against 512 merged).
+constexpr int64_t kOwnLaunch = 32768;
+
+__global__ __launch_bounds__(256, 8) void k_finalize_tiles(FinalizeArgs p, int role) {
+    __shared__ TileLds sm;
+    finalize_tile(p, p.tab[role], blockIdx.x, sm);
+}
+
 // Running accumulation (ps_stream_*): one block per (segment, tile, group of
 // 256 points of the tile).  A segment names one combination and up to two
 // pieces of the batch (the chunk completed from the carry buffer, set 0, and
@@ -259,7 +328,7 @@ __global__ __launch_bounds__(256) void k_finalize_s1(FinalizeArgs p) {
 __global__ __launch_bounds__(256) void k_accumulate(AccumArgs p) {
     const int64_t x = blockIdx.x;
     if (x >= p.n_items) return;
-    const Seg& sg = p.segs[find_seg(p.segs, p.n_segs, x)];
+    ConstSeg& sg = *find_seg(p.segs, p.n_segs, x);
     const int P = sg.tiles < 0 ? 256 : (sg.tiles >= kSym32 ? kTileX * kTileX : kTile * kTile);
     const int per_tile = P / 256;
     const int64_t local = x - sg.item0;
@@ -369,21 +438,21 @@ hipError_t launch_zscore(const double* a, const double* ae, const double* b, con
     return hipGetLastError();
 }
 
-hipError_t launch_finalize_vec(const FinalizeArgs& a, hipStream_t s) {
-    if (a.n_items <= 0) return hipSuccess;
-    k_finalize_vec<<<(unsigned)(a.n_items * kVecGroups), 256, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize_grid(const FinalizeArgs& a, hipStream_t s) {
-    if (a.n_items <= 0) return hipSuccess;
-    k_finalize_tiles<<<(unsigned)a.n_items, 256, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize_s1(const FinalizeArgs& a, hipStream_t s) {
-    if (a.n_items <= 0 || !a.s1) return hipSuccess;
-    k_finalize_s1<<<(unsigned)a.n_items, 256, 0, s>>>(a);
+hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
+    FinalizeArgs b = a;
+    b.tab[kFinS2].n_blocks *= kVecGroups;
+    if (!a.s1) b.tab[kFinS1].n_blocks = 0;
+    for (int role : {kFinS3, kFinS4}) {
+        if (b.tab[role].n_blocks < kOwnLaunch) continue;
+        k_finalize_tiles<<<(unsigned)b.tab[role].n_blocks, 256, 0, s>>>(b, role);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        b.tab[role].n_blocks = 0;
+    }
+    int64_t n = 0;
+    for (const FinalizeTable& t : b.tab) n += t.n_blocks;
+    if (n <= 0) return hipSuccess;
+    k_finalize<<<(unsigned)n, 256, 0, s>>>(b);
     return hipGetLastError();
 }
 

@@ -260,21 +260,24 @@ int s4_cross_blocks_per_cu();
 int s4_cross_mfma_blocks_per_cu();
 
 // ---------------------------------------------------------------- finalize
-struct FinalizeArgs {
-    const Seg* segs;        // items: S2 k blocks, or tiles (grid size and tile table per segment)
+// One order's finalize segments (S2 items: 256-wide k blocks; S3 and S4: 16 x 16
+// sub-blocks of tiles, grid size and tile table per segment, symmetric spectra
+// mirrored; S1: one item per (record, channel), Seg.part (and part2) the index
+// of the record's (and its interlaced twin's) first chunk in `s1`, Seg.ch[0]
+// the channel).  n_blocks: its items.
+struct FinalizeTable {
+    const Seg* segs;
     int n_segs;
-    int64_t n_items;
+    int64_t n_blocks;
+};
+enum { kFinS1 = 0, kFinS2 = 1, kFinS3 = 2, kFinS4 = 3 };
+struct FinalizeArgs {
+    FinalizeTable tab[4];   // in launch order
     const double* part;
     const float2* s1;       // per-chunk means of a_0, [C][s1_cs] (S1 only)
     int64_t s1_cs;
 };
-hipError_t launch_finalize_vec(const FinalizeArgs& a, hipStream_t s);
-// Items are 16 x 16 sub-blocks of tiles; symmetric spectra are mirrored here.
-hipError_t launch_finalize_grid(const FinalizeArgs& a, hipStream_t s);
-// S1: one item per (record, channel); Seg.part (and part2) hold the index of
-// the record's (and its interlaced twin's) first chunk in `s1`, Seg.ch[0] the
-// channel.
-hipError_t launch_finalize_s1(const FinalizeArgs& a, hipStream_t s);
+hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
 
 hipError_t launch_fill_nan(double* p, int64_t n, hipStream_t s);
 
@@ -348,15 +351,33 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Tables that no kernel of the launch writes, read through the scalar cache:
+// what every lane of a block needs alike comes in one scalar load instead of a
+// vector load per field.
+template <typename T>
+using ConstMem = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ ConstMem<T>* const_mem(const T* p) {
+    return (ConstMem<T>*)(uintptr_t)p;
+}
+using ConstSeg = ConstMem<Seg>;
+
 // Segment lookup shared by the kernels: the last segment with item0 <= v.
-__device__ __forceinline__ int find_seg(const Seg* segs, int n, int64_t v) {
+__device__ __forceinline__ ConstSeg* find_seg(const Seg* table, int n, int64_t v) {
+    ConstSeg* segs = const_mem(table);
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (segs[mid].item0 <= v) lo = mid;
         else hi = mid - 1;
     }
-    return lo;
+    return segs + lo;
+}
+
+// tile_tab[t] of a segment.
+__device__ __forceinline__ int2 tile_at(const int2* tab, int64_t t) {
+    ConstMem<int>* q = const_mem(reinterpret_cast<const int*>(tab)) + 2 * t;
+    return make_int2(q[0], q[1]);
 }
 
 }  // namespace ps

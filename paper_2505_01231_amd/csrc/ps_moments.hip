@@ -35,7 +35,7 @@ namespace {
 
 // A block's share of its segment.
 struct Block {
-    const Seg* s;
+    ConstSeg* s;
     Sched sc;
     int64_t j;              // block index within the segment
     int64_t v, v1;          // remaining units of the block's stream-K run
@@ -68,7 +68,7 @@ __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, Vie
     const int64_t per_xcd = (b.n_items + 7) >> 3;
     const int64_t x = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (x >= b.n_items) return false;
-    const Seg& s = b.segs[find_seg(b.segs, b.n_segs, x)];
+    ConstSeg& s = *find_seg(b.segs, b.n_segs, x);
     bk.s = &s;
     bk.j = x - s.item0;
     int64_t cb = 0, ce = s.n_chunks;
@@ -99,7 +99,7 @@ __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, Vie
 // components per grid point.
 template <int EDGE, int NCOMP>
 __device__ __forceinline__ bool next_item(const BatchArgs& b, Block& bk, Item& it) {
-    const Seg& s = *bk.s;
+    ConstSeg& s = *bk.s;
     int64_t t, c0, c1, slot;
     if (bk.v < bk.v1) {
         const int64_t T1 = bk.sc.T1(), W = bk.sc.W;
@@ -121,7 +121,7 @@ __device__ __forceinline__ bool next_item(const BatchArgs& b, Block& bk, Item& i
     it.c0 = bk.cbase + (int)c0;
     it.c1 = bk.cbase + (int)c1;
     if (EDGE > 0) {
-        const int2 tt = s.tile_tab[t];
+        const int2 tt = tile_at(s.tile_tab, t);
         it.k0 = tt.x * EDGE;
         it.l0 = tt.y * EDGE;
         it.part = b.part + s.part + slot * NCOMP * EDGE * EDGE;
@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
 
     Item it;
     while (next_item<kTile, 2>(p, bk, it)) {
-    const Seg& sg = *bk.s;
+    ConstSeg& sg = *bk.s;
     const int c0 = it.c0, c1 = it.c1;          // c1 > c0: pieces are never empty
     const int k0 = __builtin_amdgcn_readfirstlane(it.k0), l0 = __builtin_amdgcn_readfirstlane(it.l0);
     const char* base = wave_uniform(p.op4 + it.ch[0] * sg.op4_cs + sg.op4);
