@@ -364,6 +364,7 @@ struct BatchClass {
     // to the tile edge)
     int64_t op_chunks = 0;
     size_t op4_off = 0, p4_off = 0;
+    size_t s2c_off = 0;             // S2's chunk terms [entry][chunks][N_f]
     int rd0 = 0, n_rd = 0;          // its record descriptors in Batch.rd
 };
 
@@ -413,6 +414,11 @@ struct Batch {
     size_t off_tab = 0, off_part = 0, off_s1 = 0, total = 0;
     size_t tab_bytes = 0;
     int64_t part_doubles = 0;
+    // S2 from chunk terms that the centring pass forms: their entries by
+    // channel pair; `power`: S1 and S2 alone, no centred coefficients.
+    int8_t s2_entry[4][4];
+    int n_s2_entries = 0;
+    bool power = false;
 };
 
 size_t align64(size_t x) { return (x + 63) & ~size_t(63); }
@@ -446,13 +452,35 @@ Scales spectrum_scales(const ps_plan_s* p, const double* sum_g) {
 
 void finish_layout(const ps_plan_s* p, Batch& B);
 
-void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_output* outs, Batch& B) {
+// Which S2 pairs the centring pass forms.
+void choose_s2_terms(const ps_plan_s* p, Batch& B) {
+    std::memset(B.s2_entry, -1, sizeof B.s2_entry);
+    B.power = !p->has(3) && !p->has(4) && p->has(2) && ps::power_supported(p->C, p->m);
+    if (!p->has(2) || (!B.power && p->m > ps::kCentreRegs)) return;
+    for (int i = 0; i < p->n2(); ++i) {
+        const int a = p->c2[2 * i], b = p->c2[2 * i + 1];
+        if ((B.power || a == b) && B.s2_entry[a][b] < 0) B.s2_entry[a][b] = (int8_t)B.n_s2_entries++;
+    }
+}
+
+// Up to this many chunks the finalize adds S2's chunk terms itself, beside the
+// tiles of S3 and S4: no launch of k_s2 (5 us and its gap; 102 chunks: 98.5 -> 94.0 us
+// a call).  Few blocks do it (16 columns each), a round trip of 4 us per 128
+// chunks: with 1638 chunks the finalize takes 55 us, 28 after a k_s2 of 8.
+constexpr int64_t kS2DirectChunks = 512;
+
+// `slots`: every order leaves partial sums (running accumulation); `lean`: the
+// smallest workspace (S2 from the coefficients, no chunk terms).
+void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_output* outs, Batch& B, bool slots = false,
+                 bool lean = false) {
     const bool per_chunk = p->schedule == PS_SCHED_PER_CHUNK;
     const int m = p->m;
     const bool opt3 = p->c3opt();
     B.stride = p->interlaced ? 2 : 1;
     const int n_int = n * B.stride;
     B.ri.assign(n_int, RecInfo{});
+    std::memset(B.s2_entry, -1, sizeof B.s2_entry);
+    if (!lean) choose_s2_terms(p, B);
     // chunk counts and frame lengths
     std::vector<int> bc_of(p->fc.size(), -1);
     for (int ir = 0; ir < n_int; ++ir) {
@@ -522,6 +550,10 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
         k.p4_off = off;
         off = align256(off + (size_t)p->C * k.op_chunks * 2 * ng * sizeof(double));
     }
+    for (BatchClass& k : B.bc) {
+        k.s2c_off = off;
+        off = align256(off + (size_t)B.n_s2_entries * (per_chunk ? 1 : k.chunks) * p->fc[k.cls].Ng * sizeof(float2));
+    }
     B.coef_bytes = off;
 
     // groups (interlaced windows: batched schedule only)
@@ -538,6 +570,12 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
     int64_t part = 0;
     for (Group& G : B.groups) {
         const int r_lo = per_chunk ? G.rec : 0, r_hi = per_chunk ? G.rec + 1 : n_int;
+        // S2 combination i of internal record r is finalized from its chunk
+        // terms (both frame sets alike)
+        auto s2_direct = [&](int i, int r) {
+            const int64_t np = B.ri[r - r % B.stride].Np;
+            return !slots && !per_chunk && np <= kS2DirectChunks && B.s2_entry[p->c2[2 * i]][p->c2[2 * i + 1]] >= 0;
+        };
         // units of every segment per stage, for the block counts
         std::vector<int64_t> U2, U3, U4s, U4x;
         for (int r = r_lo; r < r_hi; ++r) {
@@ -545,7 +583,8 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
             if (Np == 0) continue;
             const FrameClass& fc = p->fc[B.ri[r].cls];
             const int kblocks = (fc.Ng + 255) / 256;
-            for (int i = 0; i < p->n2(); ++i) U2.push_back((int64_t)kblocks * Np);
+            for (int i = 0; i < p->n2(); ++i)
+                if (!s2_direct(i, r)) U2.push_back((int64_t)kblocks * Np);
             for (int i = 0; i < p->n3(); ++i) U3.push_back(fc.n_tiles[p->s3_sym(i) ? ps::kSym64 : ps::kFull64] * Np);
             for (int i = 0; i < p->n4(); ++i) {
                 bool first = true;
@@ -583,6 +622,7 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                     a.part2 = sg.part;
                     a.n_chunks2 = sg.n_chunks;
                     a.blocks2 = sg.blocks;
+                    if (a.blocks == 0) a.p4 = sg.op4;
                 }
             };
             ps::Seg base{};
@@ -610,13 +650,24 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 sg.blocks = seg_blocks(kblocks, q.Np, L2, per_chunk);
                 sg.tiles = 0;
                 for (int j = 0; j < 2; ++j) sg.ch[j] = p->c2[2 * i + j];
-                sg.part = part;
-                part += ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * 4 * 256;
+                const int entry = B.s2_entry[sg.ch[0]][sg.ch[1]];
+                const bool direct = s2_direct(i, r);
+                if (entry >= 0) {
+                    sg.op4 = (int64_t)(k.s2c_off / sizeof(float2)) +
+                             (per_chunk ? (int64_t)entry : entry * k.chunks + q.chunk0c) * Nf;
+                    sg.op4_cs = 1;
+                }
+                if (direct) {
+                    sg.blocks = 0;
+                } else {
+                    sg.part = part;
+                    part += ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * 4 * 256;
+                }
                 sg.out = o && o->d_s2 ? o->d_s2 + 2 * (int64_t)i * Nf : nullptr;
                 sg.err = o && o->d_s2_err ? o->d_s2_err + 2 * (int64_t)i * Nf : nullptr;
                 sg.scale = scl.s2;
                 sg.ncomp = 4;
-                G.s2.add(sg, sg.blocks);
+                if (!direct) G.s2.add(sg, sg.blocks);
                 finalize(G.f2, fin2, i, sg, kblocks);
             }
             for (int i = 0; i < p->n3(); ++i) {
@@ -1382,6 +1433,7 @@ ps_status launch_finalize(ps_plan_t p, const Batch& B, const Group& G, char* ws,
     f.tab[ps::kFinS3] = fin_table(G.f3, tab);
     f.tab[ps::kFinS4] = fin_table(G.f4, tab);
     f.part = reinterpret_cast<const double*>(ws + B.off_part);
+    f.ws = reinterpret_cast<const float2*>(ws);
     f.s1 = p->has(1) ? reinterpret_cast<const float2*>(ws + B.off_s1) : nullptr;
     f.s1_cs = B.chunks_tot;
     PS_HIP(ps::launch_finalize(f, st));
@@ -1447,6 +1499,8 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
     ca.s1 = p->has(1) ? reinterpret_cast<float2*>(ws + B.off_s1) : nullptr;
     ca.s1_cs = B.chunks_tot;
     ca.s1_col = p->jmax;
+    ca.s2_col0 = p->col0;
+    std::memcpy(ca.s2_entry, B.s2_entry, sizeof ca.s2_entry);
     if (p->c3opt()) {
         const double alpha = 4.0 / (m + 4.0);
         ca.alpha = (float)alpha;
@@ -1477,6 +1531,10 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
         if (p->c3opt()) {
             c.out3 = reinterpret_cast<float2*>(ws + k.coef3_off);
             c.out3_cs = k.rows3 * fc.K;
+        }
+        if (B.n_s2_entries > 0) {
+            c.s2c = reinterpret_cast<float2*>(ws + k.s2c_off);
+            c.s2_n = fc.Ng;
         }
         if (k.op_chunks > 0) {
             const int ngp = op_cols(fc.Ng);
@@ -1520,7 +1578,7 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
         }
         {
             StageTimer t(p, st, 1);
-            PS_HIP(ps::launch_centre(ca, st));
+            PS_HIP(B.power ? ps::launch_power(ca, st) : ps::launch_centre(ca, st));
         }
         s = launch_moments(p, B, B.groups[0], ws, tab, 0, 0, 0, 0, st);
         if (s != PS_OK) return s;
@@ -1564,7 +1622,7 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
             ca.cls[0].s1_chunk0 = B.ri[r].chunk0 + c;
             {
                 StageTimer t(p, st, 1);
-                PS_HIP(ps::launch_centre(ca, st));
+                PS_HIP(B.power ? ps::launch_power(ca, st) : ps::launch_centre(ca, st));
             }
             s = launch_moments(p, B, G, ws, tab, 1, (int)c, (int)c + 1, c > 0 ? 1 : 0, st);
             if (s != PS_OK) return s;
@@ -1602,6 +1660,10 @@ ps_status ps_execute_static(ps_plan_t p, const ps_record* recs, int32_t n_rec, c
     hipStream_t st = (hipStream_t)stream;
     Batch B;
     build_batch(p, recs, n_rec, outs, B);
+    if (B.total > ps::kStaticScratchBytes) {
+        B = Batch{};
+        build_batch(p, recs, n_rec, outs, B, /*slots=*/false, /*lean=*/true);
+    }
     if (B.total > ps::kStaticScratchBytes)
         return fail(PS_E_WORKSPACE, "these records need %zu bytes of workspace; the static scratch holds %zu",
                     B.total, ps::kStaticScratchBytes);
@@ -2039,7 +2101,7 @@ void build_stream_batch(const ps_accum_s* a, int64_t n, Batch& B) {
     r.n_samples = n;
     r.channel_stride = a->stage_stride;
     r.dtype = a->dtype;
-    build_batch(p, &r, 1, nullptr, B);
+    build_batch(p, &r, 1, nullptr, B, /*slots=*/true);
     Group& G = B.groups[0];
     const int64_t TT = (int64_t)ps::kTile * ps::kTile, TX = (int64_t)ps::kTileX * ps::kTileX;
     auto add = [&](const SegTable& f, const std::vector<int64_t>& off, int64_t points, bool vec) {

@@ -74,6 +74,7 @@ __device__ __forceinline__ void add_slots(double (&s)[4], const double* q, uint3
 // (of each frame set); the 16 group sums are then added in LDS in group order
 // (a fixed order, so the result does not depend on timing).
 constexpr int kVecGroups = 16;
+constexpr int kTermBatch = 8;
 
 struct VecLds {
     double red[kVecGroups][8][16];
@@ -95,8 +96,27 @@ __device__ __forceinline__ void finalize_vec(const FinalizeArgs& p, const Finali
         if (set && !two) break;
         const int64_t W = set ? sg.n_chunks2 : sg.n_chunks;
         int64_t s0 = 0, ns = 0;
-        if (W > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, t, s0, ns);
+        if (W > 0 && sg.blocks > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, t, s0, ns);
         double a[4] = {0, 0, 0, 0};
+        if (sg.blocks == 0) {       // no partial sums: thread group g adds the chunk terms of chunks g, g + 16, ...
+            const float2* q = p.ws + (set ? sg.p4 : sg.op4) + k;
+            for (int64_t c = g; k < sg.Nf && c < W; c += kTermBatch * kVecGroups) {
+                float2 x[kTermBatch];
+#pragma unroll
+                for (int u = 0; u < kTermBatch; ++u) {
+                    const int64_t cu = c + u * kVecGroups;
+                    x[u] = cu < W ? q[cu * sg.Nf] : make_float2(0.f, 0.f);
+                }
+#pragma unroll
+                for (int u = 0; u < kTermBatch; ++u) {
+                    a[0] += x[u].x;
+                    a[1] += x[u].y;
+                    a[2] = fma((double)x[u].x, (double)x[u].x, a[2]);
+                    a[3] = fma((double)x[u].y, (double)x[u].y, a[3]);
+                }
+            }
+            ns = 0;
+        }
         add_slots<4>(a, p.part + (set ? sg.part2 : sg.part) + s0 * 4 * 256, (uint32_t)(g * 4 * 256 + kl),
                      ((int)ns - g + kVecGroups - 1) / kVecGroups, kVecGroups * 4 * 256, 256);
 #pragma unroll

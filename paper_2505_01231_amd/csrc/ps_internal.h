@@ -143,6 +143,10 @@ struct CentreClass {
     double* p4;             // [C][n_chunks][op4_cols][2]: (p, s^2) per column
     int64_t p4_cs;          // double elements between channels
     int op4_cols;
+    // S2's chunk terms sum_f a'_k b'*_k (null: none), [entry][n_chunks][s2_n]
+    // with the entries of CentreArgs.s2_entry
+    float2* s2c;
+    int s2_n;
     int64_t block0;         // first block of the class
 };
 struct CentreArgs {
@@ -154,8 +158,17 @@ struct CentreArgs {
     int64_t s1_cs;
     int s1_col;
     float alpha, mu;
+    int s2_col0;            // column of S2's grid index 0
+    int8_t s2_entry[4][4];  // entry of channels (a, b) in s2c, -1: none
 };
+// The centring pass.  With s2c it also forms S2's chunk terms of channels with
+// themselves (m <= kCentreRegs).
+constexpr int kCentreRegs = 16;
 hipError_t launch_centre(const CentreArgs& a, hipStream_t s);
+// S1 and S2 alone: the chunk terms of every pair in s2_entry, nothing written
+// back.  Takes n_channels frames_held(m) <= 64, m <= 32.
+inline bool power_supported(int n_channels, int m) { return m <= 32 && n_channels * (m <= 16 ? 16 : 32) <= 64; }
+hipError_t launch_power(const CentreArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- work decomposition
 // A segment's work is T tiles x W chunks of (tile, chunk) units spread over B
@@ -197,8 +210,14 @@ struct Seg {
     int64_t item0;          // first work item (block) of the segment
     int64_t coef;           // float2 offset of the record's chunk 0 in the coefficient region
     int64_t cs;             // float2 elements between channels of the record's coefficient block
-    int64_t op4, op4_cs;    // S4 operand records of the record's chunk 0 (uint32 offset), channel stride
-    int64_t p4, p4_cs;      // and its (column sum of P, scale s^2) pairs (double offset), channel stride
+    // S4 operand records of the record's chunk 0 (uint32 offset), channel stride.
+    // S2: chunk terms of the record's chunk 0 (float2 offset from the workspace
+    // start), op4_cs = 1: the segment takes those in place of coefficients.
+    int64_t op4, op4_cs;
+    // and its (column sum of P, scale s^2) pairs (double offset), channel stride.
+    // S2 finalize with blocks == 0 (no partial sums: the chunk terms themselves
+    // are added): p4 the shifted frame set's chunk terms.
+    int64_t p4, p4_cs;
     const int2* tile_tab;   // the grid's tile table (tile t -> (kt, lt)); by `tiles` and the grid size
     int32_t K;              // coefficients per frame of the record's frame length
     int32_t Nf;             // points per grid axis of the record's spectra
@@ -274,6 +293,7 @@ enum { kFinS1 = 0, kFinS2 = 1, kFinS3 = 2, kFinS4 = 3 };
 struct FinalizeArgs {
     FinalizeTable tab[4];   // in launch order
     const double* part;
+    const float2* ws;       // workspace start (S2's chunk terms)
     const float2* s1;       // per-chunk means of a_0, [C][s1_cs] (S1 only)
     int64_t s1_cs;
 };

@@ -141,6 +141,7 @@ __device__ __forceinline__ bool next_item(const BatchArgs& b, Block& bk, Item& i
 // pair of channels keeps the per-frame loop (its two register arrays would
 // cost occupancy for a kernel of a few microseconds).
 constexpr int kS2Regs = 16;
+constexpr int kS2Batch = 8;      // chunk terms loaded at once
 
 __global__ __launch_bounds__(256) void k_s2(BatchArgs p) {
     Block bk;
@@ -156,7 +157,23 @@ __global__ __launch_bounds__(256) void k_s2(BatchArgs p) {
         const float2* B = v.coef + it.ch[1] * v.cs;
         const bool same = it.ch[0] == it.ch[1];      // S2 of one channel: one load per frame
         double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        for (int c = it.c0; c < c_end; ++c) {
+        if (bk.s->op4_cs) {     // the centring pass formed the chunk terms
+            const float2* t = p.coef + bk.s->op4 + k - (p.per_chunk ? (int64_t)p.win_lo * v.Nf : 0);
+            for (int c = it.c0; c < c_end; c += kS2Batch) {
+                float2 x[kS2Batch];
+#pragma unroll
+                for (int u = 0; u < kS2Batch; ++u)
+                    x[u] = c + u < c_end ? t[(int64_t)(c + u) * v.Nf] : make_float2(0.f, 0.f);
+#pragma unroll
+                for (int u = 0; u < kS2Batch; ++u) {
+                    s0 += x[u].x;
+                    s1 += x[u].y;
+                    s2 += (double)x[u].x * x[u].x;
+                    s3 += (double)x[u].y * x[u].y;
+                }
+            }
+        }
+        for (int c = bk.s->op4_cs ? c_end : it.c0; c < c_end; ++c) {
             const int64_t base = v.off + (int64_t)c * v.m * v.K + k;
             float re = 0.f, im = 0.f;
             if (v.m <= kS2Regs && same) {
