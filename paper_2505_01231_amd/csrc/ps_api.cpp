@@ -1362,8 +1362,9 @@ ps_status upload_tables(ps_plan_t p, const Batch& B, char* d_tab, hipStream_t st
 }
 
 ps::BatchArgs batch_args(const ps_plan_s* p, const Batch& B, const SegTable& t, char* ws, const char* tab,
-                         int per_chunk, int win_lo, int win_hi, int accumulate) {
+                         int per_chunk, int win_lo, int win_hi, int accumulate, int finalized) {
     ps::BatchArgs a{};
+    a.finalized = finalized;
     a.segs = reinterpret_cast<const ps::Seg*>(tab + t.dev_off);
     a.n_segs = (int)t.v.size();
     a.n_items = t.n_items;
@@ -1389,14 +1390,14 @@ ps::FinalizeTable fin_table(const SegTable& t, const char* tab) {
 
 // The moment stages of one group (one launch each).
 ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, const char* tab, int per_chunk,
-                         int win_lo, int win_hi, int accumulate, hipStream_t st) {
+                         int win_lo, int win_hi, int accumulate, int finalized, hipStream_t st) {
     if (G.s2.n_items) {
         StageTimer t(p, st, 2);
-        PS_HIP(ps::launch_s2(batch_args(p, B, G.s2, ws, tab, per_chunk, win_lo, win_hi, accumulate), st));
+        PS_HIP(ps::launch_s2(batch_args(p, B, G.s2, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized), st));
     }
     if (G.s3.n_items) {
         StageTimer t(p, st, 3);
-        ps::BatchArgs a = batch_args(p, B, G.s3, ws, tab, per_chunk, win_lo, win_hi, accumulate);
+        ps::BatchArgs a = batch_args(p, B, G.s3, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized);
         // the c3^(opt) rows: m shifted frames and one mean row per chunk
         // (the segments point at their blocks)
         if (p->c3opt()) a.m = p->m + 1;
@@ -1404,7 +1405,7 @@ ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, 
     }
     if (G.s4s.n_items) {
         StageTimer t(p, st, 4);
-        ps::BatchArgs a = batch_args(p, B, G.s4s, ws, tab, per_chunk, win_lo, win_hi, accumulate);
+        ps::BatchArgs a = batch_args(p, B, G.s4s, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized);
         if (p->s4_pre) {                // operands split by the centring pass
             a.op4 = reinterpret_cast<const uint32_t*>(ws);
             a.p4 = reinterpret_cast<const double*>(ws);
@@ -1420,7 +1421,7 @@ ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, 
     if (G.s4x.n_items) {
         StageTimer t(p, st, 4);
         PS_HIP((p->precision == PS_PREC_BF16X3 ? ps::launch_s4_cross_mfma : ps::launch_s4_cross)(
-            batch_args(p, B, G.s4x, ws, tab, per_chunk, win_lo, win_hi, accumulate), st));
+            batch_args(p, B, G.s4x, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized), st));
     }
     return PS_OK;
 }
@@ -1580,7 +1581,7 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
             StageTimer t(p, st, 1);
             PS_HIP(B.power ? ps::launch_power(ca, st) : ps::launch_centre(ca, st));
         }
-        s = launch_moments(p, B, B.groups[0], ws, tab, 0, 0, 0, 0, st);
+        s = launch_moments(p, B, B.groups[0], ws, tab, 0, 0, 0, 0, acc == nullptr, st);
         if (s != PS_OK) return s;
         if (acc) {
             const Group& G = B.groups[0];
@@ -1624,7 +1625,7 @@ ps_status enqueue_all(ps_plan_t p, const Batch& B, const ps_record* recs, int32_
                 StageTimer t(p, st, 1);
                 PS_HIP(B.power ? ps::launch_power(ca, st) : ps::launch_centre(ca, st));
             }
-            s = launch_moments(p, B, G, ws, tab, 1, (int)c, (int)c + 1, c > 0 ? 1 : 0, st);
+            s = launch_moments(p, B, G, ws, tab, 1, (int)c, (int)c + 1, c > 0 ? 1 : 0, 0, st);
             if (s != PS_OK) return s;
         }
         s = launch_finalize(p, B, G, ws, tab, st);

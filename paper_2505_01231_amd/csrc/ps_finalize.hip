@@ -190,7 +190,10 @@ __device__ __forceinline__ void finalize_tile(const FinalizeArgs& p, const Final
         if (W > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, tile, s0, ns);
         double s[4] = {0, 0, 0, 0};
         const double* q = p.part + (set ? sg.part2 : sg.part) + s0 * ncomp * TT;
-        if (ncomp == 4) add_slots<4>(s, q, idx, (int)ns, 4 * TT, TT);
+        if (W == 1) {       // one slot, no squares in it
+            s[0] = q[idx];
+            if (ncomp == 4) s[1] = q[TT + idx];
+        } else if (ncomp == 4) add_slots<4>(s, q, idx, (int)ns, 4 * TT, TT);
         else add_slots<2>(s, q, idx, (int)ns, 2 * TT, TT);
         double r_m, r_s, i_m = 0.0, i_s = 0.0;
         if (ncomp == 4) {

@@ -256,6 +256,10 @@ struct BatchArgs {
     // processed and chunk c sits at frame (c - win_lo) m of the region.
     int per_chunk, win_lo, win_hi;
     int accumulate;         // add to the partial sums instead of overwriting
+    // The partial sums are finalized after this launch: a segment of one chunk
+    // leaves the sums of its squares (the later half of the components)
+    // unwritten, and the finalize does not read them.
+    int finalized;
     // S4 kernels form v = M4 - gamma (p_k p_l + |Q|^2 + |R|^2) in FP64:
     // gamma = (m-1)/(m(m+1)) for the k-statistic, 1/m for the natural estimator
     double gamma;

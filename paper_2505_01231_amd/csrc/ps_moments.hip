@@ -62,6 +62,7 @@ struct View {
     const float2* coef;
     int64_t cs, off;
     int K, m, Nf, col0, col3;
+    bool lone;              // one chunk: its squares are not wanted (no error bar)
 };
 
 __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, View& v) {
@@ -91,6 +92,7 @@ __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, Vie
     v.K = s.K;
     v.m = b.m;
     v.Nf = s.Nf;
+    v.lone = b.finalized && s.n_chunks == 1;
     return true;
 }
 
@@ -321,6 +323,11 @@ __device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, const
         }
     }
 
+    // (A piece's 128 KB: 10^6 samples at N_f = 200 are 512 pieces of two chunks.
+    // The end after half the components also keeps the compiler from forming
+    // every address at once, which spilled 91 registers per piece: 33 -> 22 us
+    // there, and 175 -> 81 for 409 records of one chunk at N_f = 256, where the
+    // squares of one chunk are 0.27 GB.)
     double* o = it.part;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -329,6 +336,7 @@ __device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, const
             const int idx = (ti + 16 * u) * kTile + tj + 16 * w;
 #pragma unroll
             for (int comp = 0; comp < 4; ++comp) {
+                if (comp >= 2 && v.lone) break;
                 double val = acc[u * 4 + w][comp];
                 if (p.accumulate) val += o[comp * kTile * kTile + idx];
                 o[comp * kTile * kTile + idx] = val;
@@ -515,6 +523,7 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
         const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + rowL;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
+            if (comp >= 1 && v.lone) break;
             double val = acc[r][comp];
             if (p.accumulate) val += o[comp * kTile * kTile + idx];
             o[comp * kTile * kTile + idx] = val;
@@ -751,6 +760,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
         const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + 32 * (w & 1) + r32;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
+            if (comp >= 1 && v.lone) break;
             double val = acc[r][comp];
             if (p.accumulate) val += o[comp * kTile * kTile + idx];
             o[comp * kTile * kTile + idx] = val;
@@ -948,6 +958,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16(BatchArgs p) {
             const int idx = (w * 16 + 4 * lg + e) * kTile + lb * 16 + li;
 #pragma unroll
             for (int comp = 0; comp < 2; ++comp) {
+                if (comp >= 1 && v.lone) break;
                 double val = acc[lb][e][comp];
                 if (p.accumulate) val += o[comp * kTile * kTile + idx];
                 o[comp * kTile * kTile + idx] = val;
@@ -1284,6 +1295,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
         const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + 32 * (w & 1) + r32;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
+            if (comp >= 1 && v.lone) break;
             double val = acc[r][comp];
             if (p.accumulate) val += o[comp * kTile * kTile + idx];
             o[comp * kTile * kTile + idx] = val;
@@ -1463,6 +1475,7 @@ __global__ __launch_bounds__(kS4XThreads, 3) void k_s4_cross_f32(BatchArgs p) {
         const int idx = (16 * (w >> 1) + 4 * g + q) * kTileX + rowB;
 #pragma unroll
         for (int comp = 0; comp < 4; ++comp) {
+            if (comp >= 2 && v.lone) break;
             double val = acc[q][comp];
             if (p.accumulate) val += o[comp * TT + idx];
             o[comp * TT + idx] = val;
@@ -1748,6 +1761,7 @@ __device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v,
             const int idx = (16 * (w >> 1) + 4 * lg + e) * kTileX + rowB;
 #pragma unroll
             for (int comp = 0; comp < 4; ++comp) {
+                if (comp >= 2 && v.lone) break;
                 double val = acc[out][e][comp];
                 if (p.accumulate) val += o[comp * TT + idx];
                 o[comp * TT + idx] = val;
