@@ -430,25 +430,211 @@ __global__ __launch_bounds__(256) void k_window_dft(FftArgs args) {
 // The same transform in two stages when N = N1 N2 factors well (N1 <= N2,
 // both from dft_n1): with n = N2 n1 + n2 and k = k1 + N1 k2 (Cooley-Tukey),
 //   Y[k1][n2] = exp(+2 pi j n2 k1 / N) sum_{n1 < N1} w[N2 n1 + n2] exp(+2 pi j n1 k1 / N1),
-//   a_{k1 + N1 k2} = sum_{n2 < N2} Y[k1][n2] exp(+2 pi j n2 k2 / N2),
-// N (N1 + N2) products instead of N K.  One block per frame and channel: the
-// windowed frame (FP32), the two stages' exponentials and Y (FP32, rows
-// padded by one) sit in LDS, every sum is accumulated in FP64, every
+//   a_{k1 + N1 k2} = sum_{n2 < N2} Y[k1][n2] exp(+2 pi j n2 k2 / N2).
+// The windowed samples and Y are FP32 in LDS, every sum is FP64, every
 // exponential comes from the FP64 table of exp(+2 pi j t / N)
 // (exp(+2 pi j t / N1) = entry t N2, exp(+2 pi j t / N2) = entry t N1).
-// LDS (dynamic): the N samples (FP32), the exponentials of the two stages
-// exp(+2 pi j t / N1), t < N1, and exp(+2 pi j t / N2), t < N2 (FP64), then Y.
-__host__ __device__ constexpr size_t dft2_sx_bytes(int N) { return ((size_t)N * 4 + 15) / 16 * 16; }
+//
+// Both stages add their terms n and N' - n together (N' = N1, N2):
+//   sum_n x_n exp(+j th n) = x_0 + sum_{n < N'/2} (x_n + x_{N'-n}) cos(th n) + j (x_n - x_{N'-n}) sin(th n)
+// (and the term n = N'/2 of an even N'), two FMAs per pair and output in stage
+// 1, whose samples are real and whose outputs k1 and N1 - k1 share them, four
+// in stage 2.  A wave takes 64 columns n2 (rows k1 in stage 2) and a tile of
+// frequencies that all its lanes share (nine in stage 1, seven in stage 2: at
+// N = 1536 one tile per wave): the exponentials are scalar loads and the pair's
+// sums serve the whole tile.  dft2_frames frames per block fill the lanes when
+// N1 is small; twice as many, or one, cost 30 and 40 % (LDS, idle lanes).
+// Bound: nothing saturated; without stage 1, stage 2, the samples or the gathers
+// of exp(n2 k1) 30, 50, 25 and 16 us less of 156.  Measured (2^24 samples,
+// N = 1536, K = 769): 142 us; with a product per term and its operands from LDS
+// 346 us; at 2^23 samples, N = 300, 1000, 3000, 6144: 70, 68, 79 and 120 us
+// against 107, 115, 202 and 345.
+constexpr int kDft2Q = 7, kDft2Q1 = 9;
+__host__ __device__ constexpr size_t dft2_frame_bytes(int N, int N1) {
+    return (size_t)N * 4 + (size_t)N1 * (N / N1 + 1) * 8;
+}
+// Frames per block: the lanes' 64 rows, at most 40 KB of LDS (four blocks per CU).
+__host__ __device__ constexpr int dft2_frames(int N, int N1) {
+    const int by_rows = 64 / N1, by_lds = (int)(40960 / dft2_frame_bytes(N, N1));
+    const int f = by_rows < by_lds ? by_rows : by_lds;
+    return f > 1 ? f : 1;
+}
+__host__ __device__ constexpr size_t dft2_sx_bytes(int N, int N1) {
+    return ((size_t)dft2_frames(N, N1) * N * 4 + 15) / 16 * 16;
+}
+// LDS (dynamic): the frames' windowed samples (FP32), then Y, N1 rows of N2 + 1 per frame.
 __host__ __device__ constexpr size_t dft2_lds_bytes(int N, int N1) {
-    return dft2_sx_bytes(N) + (size_t)(N1 + N / N1) * 16 + (size_t)N1 * (N / N1 + 1) * 8;
+    return dft2_sx_bytes(N, N1) + (size_t)dft2_frames(N, N1) * N1 * (N / N1 + 1) * 8;
+}
+
+// A frame's windowed samples, six of a thread's in flight at once.
+template <typename T>
+__device__ __forceinline__ void dft2_stage(float* sx, const T* x, const float* g, int N) {
+    constexpr int kBatch = 6;
+    for (int i0 = threadIdx.x; i0 < N; i0 += 256 * kBatch) {
+        T v[kBatch];
+        float w[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int i = i0 + 256 * u;
+            v[u] = i < N ? x[i] : T(0);
+            w[u] = i < N ? g[i] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (i0 + 256 * u < N) sx[i0 + 256 * u] = (float)((double)w[u] * (double)v[u]);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_window_dft2(FftArgs args) {
     const FftClass& a = args.cls[0];
     HIP_DYNAMIC_SHARED(double2, dyn)
+    const int N = a.dft_n, N1 = a.dft_n1, N2 = N / N1, K = a.K, F = dft2_frames(N, N1);
+    float* sx = reinterpret_cast<float*>(dyn);                        // windowed samples [F][N]
+    float2* sy = reinterpret_cast<float2*>(reinterpret_cast<char*>(dyn) + dft2_sx_bytes(N, N1));    // Y [F][N1][N2 + 1]
+    // exp(+2 pi j t / N) by the byte offset 16 t, the same in all lanes; a step
+    // mod the table's length (both below it: the smaller of the sum and,
+    // unsigned, the sum less the length).  Packed copies of either stage's
+    // entries measured the same.
+    const uint32_t wrap = 16u * N;
+    ConstMem<char>* tw = const_mem(reinterpret_cast<const char*>(a.tw64));
+    auto step = [wrap](uint32_t t, uint32_t by) {
+        const uint32_t u = t + by, v = u - wrap;
+        return v < u ? v : u;
+    };
+    auto twiddle = [tw](uint32_t t) {
+        typedef double pair_t __attribute__((vector_size(16)));
+        const pair_t w = *reinterpret_cast<ConstMem<pair_t>*>(tw + t);
+        return make_double2(w[0], w[1]);
+    };
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
+    const int64_t g0 = a.g_lo + (int64_t)blockIdx.x * F;
+    const int c = blockIdx.y;
+    if (g0 >= a.g_hi) return;                            // (block-uniform)
+    const int nf = (int)(a.g_hi - g0 < F ? a.g_hi - g0 : F);
+    for (int f = 0; f < nf; ++f) {
+        RecDesc rec = a.single;
+        if (a.recs) {
+            int lo = 0, hi = a.n_recs - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (a.recs[mid].frame0 <= g0 + f) lo = mid;
+                else hi = mid - 1;
+            }
+            rec = a.recs[lo];
+        }
+        const int64_t off = c * rec.chan_stride + (g0 + f - rec.frame0) * N;
+        if (rec.dtype == 0) dft2_stage(sx + f * N, static_cast<const float*>(rec.data) + off, a.g, N);
+        else if (rec.dtype == 1) dft2_stage(sx + f * N, static_cast<const double*>(rec.data) + off, a.g, N);
+        else dft2_stage(sx + f * N, static_cast<const int16_t*>(rec.data) + off, a.g, N);
+    }
+    lds_barrier();
+
+    // stage 1: frequencies q and N1 - q, q <= N1 / 2, of 64 columns (frame, n2)
+    {
+        const int n_tiles = (N1 / 2 + kDft2Q1) / kDft2Q1, n_cols = nf * N2;
+        const int n_items = n_tiles * ((n_cols + 63) / 64);
+        for (int it = wave; it < n_items; it += 4) {
+            const int q0 = it % n_tiles * kDft2Q1, col = it / n_tiles * 64 + lane;
+            const bool live = col < n_cols;
+            const int f = live ? col / N2 : 0, n2 = live ? col - f * N2 : 0;
+            const float* x = sx + f * N + n2;
+            double re[kDft2Q1], im[kDft2Q1];
+            uint32_t t[kDft2Q1], by[kDft2Q1];            // entries n q N2 and q N2 mod N
+            const double x0 = x[0], xm = N1 % 2 ? 0.0 : (double)x[N1 / 2 * N2];
+#pragma unroll
+            for (int j = 0; j < kDft2Q1; ++j) {
+                re[j] = x0 + ((q0 + j) & 1 ? -xm : xm);
+                im[j] = 0.0;
+                t[j] = 0;
+                by[j] = 16u * N2 * ((q0 + j) % N1);
+            }
+            for (int n = 1; n < N1 - n; ++n) {
+                const double u = x[n * N2], v = x[(N1 - n) * N2];
+                const double e = u + v, o = u - v;
+#pragma unroll
+                for (int j = 0; j < kDft2Q1; ++j) {
+                    t[j] = step(t[j], by[j]);
+                    const double2 w = twiddle(t[j]);
+                    re[j] = fma(e, w.x, re[j]);
+                    im[j] = fma(o, w.y, im[j]);
+                }
+            }
+            if (!live) continue;
+            float2* y = sy + f * N1 * (N2 + 1) + n2;
+#pragma unroll
+            for (int j = 0; j < kDft2Q1; ++j) {
+                const int q = q0 + j;
+                if (2 * q > N1) break;
+                const double2 w = a.tw64[n2 * q];        // n2 k1 < N
+                y[q * (N2 + 1)] = make_float2((float)(re[j] * w.x - im[j] * w.y), (float)(re[j] * w.y + im[j] * w.x));
+                if (q == 0 || 2 * q == N1) continue;
+                const double2 z = a.tw64[n2 * (N1 - q)];
+                y[(N1 - q) * (N2 + 1)] =
+                    make_float2((float)(re[j] * z.x + im[j] * z.y), (float)(re[j] * z.y - im[j] * z.x));
+            }
+        }
+    }
+    lds_barrier();
+
+    // stage 2: coefficients k = k1 + N1 k2 < K of 64 rows (frame, k1)
+    const int n_k2 = (K + N1 - 1) / N1, n_tiles = (n_k2 + kDft2Q - 1) / kDft2Q, n_rows = nf * N1;
+    const int n_items = n_tiles * ((n_rows + 63) / 64);
+    for (int it = wave; it < n_items; it += 4) {
+        const int q0 = it % n_tiles * kDft2Q, row = it / n_tiles * 64 + lane;
+        const bool live = row < n_rows;
+        const int f = live ? row / N1 : 0, k1 = live ? row - f * N1 : 0;
+        const float2* y = sy + (f * N1 + k1) * (N2 + 1);
+        double xr[kDft2Q], xi[kDft2Q];
+        uint32_t t[kDft2Q], by[kDft2Q];                  // entries n k2 N1 and k2 N1 mod N
+        const float2 y0 = y[0], ym = N2 % 2 ? make_float2(0.f, 0.f) : y[N2 / 2];
+#pragma unroll
+        for (int j = 0; j < kDft2Q; ++j) {
+            const double s = (q0 + j) & 1 ? -1.0 : 1.0;
+            xr[j] = fma(s, (double)ym.x, (double)y0.x);
+            xi[j] = fma(s, (double)ym.y, (double)y0.y);
+            t[j] = 0;
+            by[j] = 16u * N1 * ((q0 + j) % N2);
+        }
+        for (int n = 1; n < N2 - n; ++n) {
+            const float2 u = y[n], v = y[N2 - n];
+            const double er = (double)u.x + (double)v.x, ei = (double)u.y + (double)v.y;
+            const double dr = (double)u.x - (double)v.x, di = (double)u.y - (double)v.y;
+#pragma unroll
+            for (int j = 0; j < kDft2Q; ++j) {
+                t[j] = step(t[j], by[j]);
+                const double2 w = twiddle(t[j]);
+                xr[j] = fma(er, w.x, fma(-di, w.y, xr[j]));
+                xi[j] = fma(ei, w.x, fma(dr, w.y, xi[j]));
+            }
+        }
+        if (!live) continue;
+        float2* o = a.out + c * a.out_chan_stride + (g0 + f - a.out_g0) * K;
+#pragma unroll
+        for (int j = 0; j < kDft2Q; ++j) {
+            const int k = k1 + N1 * (q0 + j);
+            if (k < K) o[k] = make_float2((float)xr[j], (float)xi[j]);
+        }
+    }
+}
+
+// The two stages with a product per term and outputs spread over all threads,
+// whatever N1: for lengths with a small N1 and a large N2 (8 x 1021), whose
+// block holds too few rows for the lanes of k_window_dft2.
+// LDS (dynamic): the N samples (FP32), the exponentials of the two stages
+// exp(+2 pi j t / N1), t < N1, and exp(+2 pi j t / N2), t < N2 (FP64), then Y.
+__host__ __device__ constexpr size_t dft2_few_sx_bytes(int N) { return ((size_t)N * 4 + 15) / 16 * 16; }
+__host__ __device__ constexpr size_t dft2_few_lds_bytes(int N, int N1) {
+    return dft2_few_sx_bytes(N) + (size_t)(N1 + N / N1) * 16 + (size_t)N1 * (N / N1 + 1) * 8;
+}
+
+__global__ __launch_bounds__(256) void k_window_dft2_few(FftArgs args) {
+    const FftClass& a = args.cls[0];
+    HIP_DYNAMIC_SHARED(double2, dyn)
     const int N = a.dft_n, N1 = a.dft_n1, N2 = N / N1, K = a.K;
     float* sx = reinterpret_cast<float*>(dyn);                        // windowed samples of the frame
-    double2* sw1 = dyn + dft2_sx_bytes(N) / 16;                       // exp(+2 pi j t / N1)
+    double2* sw1 = dyn + dft2_few_sx_bytes(N) / 16;                       // exp(+2 pi j t / N1)
     double2* sw2 = sw1 + N1;                                          // exp(+2 pi j t / N2)
     float2* sy = reinterpret_cast<float2*>(sw2 + N2);                 // Y, N1 rows of N2 + 1
 
@@ -517,10 +703,17 @@ hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
     if (c.dft_n1 > 0) {                 // two stages, N = N1 N2
         const int n2 = c.dft_n / c.dft_n1;
         if (n2 * c.dft_n1 != c.dft_n || c.dft_n1 > n2) return hipErrorInvalidValue;
-        const size_t lds = dft2_lds_bytes(c.dft_n, c.dft_n1);
-        if (lds > 160 * 1024) return hipErrorInvalidValue;
         if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
-        k_window_dft2<<<dim3((unsigned)n, a.n_channels), 256, lds, st>>>(a);
+        // A quarter of the lanes with rows: 24 rows take 76 us against 156 (2^22
+        // samples, N = 1016 = 8 x 127, three frames) and 87 against 154 (N = 3336 =
+        // 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against
+        // 303 (N = 4072 = 8 x 509).
+        const int F = dft2_frames(c.dft_n, c.dft_n1);
+        const bool few = F * c.dft_n1 < 16;
+        const size_t lds = few ? dft2_few_lds_bytes(c.dft_n, c.dft_n1) : dft2_lds_bytes(c.dft_n, c.dft_n1);
+        if (lds > 160 * 1024) return hipErrorInvalidValue;
+        if (few) k_window_dft2_few<<<dim3((unsigned)n, a.n_channels), 256, lds, st>>>(a);
+        else k_window_dft2<<<dim3((unsigned)((n + F - 1) / F), a.n_channels), 256, lds, st>>>(a);
         return hipGetLastError();
     }
     const int64_t bx = (n + kDftFrames - 1) / kDftFrames, bz = (c.K + kDftBins - 1) / kDftBins;

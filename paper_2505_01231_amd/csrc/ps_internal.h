@@ -386,6 +386,16 @@ __device__ __forceinline__ ConstMem<T>* const_mem(const T* p) {
 }
 using ConstSeg = ConstMem<Seg>;
 
+// A value that every lane of the wave holds alike, as a scalar.  (Kernel sources
+// are also compiled for the CPU, a thread per lane, by the host tests.)
+__device__ __forceinline__ int wave_uniform(int x) {
+#if defined(__HIP__)
+    return __builtin_amdgcn_readfirstlane(x);
+#else
+    return x;
+#endif
+}
+
 // Segment lookup shared by the kernels: the last segment with item0 <= v.
 __device__ __forceinline__ ConstSeg* find_seg(const Seg* table, int n, int64_t v) {
     ConstSeg* segs = const_mem(table);
