@@ -435,20 +435,24 @@ __global__ __launch_bounds__(256) void k_window_dft(FftArgs args) {
 // exponential comes from the FP64 table of exp(+2 pi j t / N)
 // (exp(+2 pi j t / N1) = entry t N2, exp(+2 pi j t / N2) = entry t N1).
 //
-// Both stages add their terms n and N' - n together (N' = N1, N2):
-//   sum_n x_n exp(+j th n) = x_0 + sum_{n < N'/2} (x_n + x_{N'-n}) cos(th n) + j (x_n - x_{N'-n}) sin(th n)
-// (and the term n = N'/2 of an even N'), two FMAs per pair and output in stage
-// 1, whose samples are real and whose outputs k1 and N1 - k1 share them, four
-// in stage 2.  A wave takes 64 columns n2 (rows k1 in stage 2) and a tile of
+// Stage 1 takes its samples, which are real, in order, each for an output k1
+// and its conjugate N1 - k1.  (The order matters: where the exponentials are
+// multiples of 60 degrees Y is a dyadic number up to FP64 rounding, often
+// halfway between two FP32 values, and another order rounds it the other way.)
+// Stage 2 adds the terms n and N2 - n together,
+//   sum_n y_n exp(j th n) = y_0 + sum_{n < N2/2} (y_n + y_{N2-n}) cos(th n) + j (y_n - y_{N2-n}) sin(th n)
+// (and y_{N2/2} (-1)^{k2}), four FMAs per pair.  A wave takes 64 columns n2
+// (rows k1 in stage 2) and a tile of
 // frequencies that all its lanes share (nine in stage 1, seven in stage 2: at
-// N = 1536 one tile per wave): the exponentials are scalar loads and the pair's
-// sums serve the whole tile.  dft2_frames frames per block fill the lanes when
-// N1 is small; twice as many, or one, cost 30 and 40 % (LDS, idle lanes).
-// Bound: nothing saturated; without stage 1, stage 2, the samples or the gathers
-// of exp(n2 k1) 30, 50, 25 and 16 us less of 156.  Measured (2^24 samples,
-// N = 1536, K = 769): 142 us; with a product per term and its operands from LDS
-// 346 us; at 2^23 samples, N = 300, 1000, 3000, 6144: 70, 68, 79 and 120 us
-// against 107, 115, 202 and 345.
+// N = 1536 one tile per wave): the exponentials are scalar loads and the
+// samples, or the pair's sums, serve the whole tile.  dft2_frames frames per
+// block fill the lanes when N1 is small; twice as many, or one, cost 30 and 40 %
+// (LDS, idle lanes).
+// Bound: nothing saturated; the samples, stage 1, stage 2 and the gathers of
+// exp(n2 k1) run one after another, with four blocks per CU to overlap them.
+// Measured (2^24 samples, N = 1536, K = 769): 159 us; with a product per output
+// and term, its operands from LDS, 346 us.  2^22 samples, N = 296, 1016, 3336,
+// 7992: 43, 83, 95 and 180 us against 58, 158, 152 and 377.
 constexpr int kDft2Q = 7, kDft2Q1 = 9;
 __host__ __device__ constexpr size_t dft2_frame_bytes(int N, int N1) {
     return (size_t)N * 4 + (size_t)N1 * (N / N1 + 1) * 8;
@@ -542,23 +546,20 @@ __global__ __launch_bounds__(256) void k_window_dft2(FftArgs args) {
             const float* x = sx + f * N + n2;
             double re[kDft2Q1], im[kDft2Q1];
             uint32_t t[kDft2Q1], by[kDft2Q1];            // entries n q N2 and q N2 mod N
-            const double x0 = x[0], xm = N1 % 2 ? 0.0 : (double)x[N1 / 2 * N2];
 #pragma unroll
             for (int j = 0; j < kDft2Q1; ++j) {
-                re[j] = x0 + ((q0 + j) & 1 ? -xm : xm);
-                im[j] = 0.0;
+                re[j] = im[j] = 0.0;
                 t[j] = 0;
                 by[j] = 16u * N2 * ((q0 + j) % N1);
             }
-            for (int n = 1; n < N1 - n; ++n) {
-                const double u = x[n * N2], v = x[(N1 - n) * N2];
-                const double e = u + v, o = u - v;
+            for (int n = 0; n < N1; ++n) {
+                const double u = x[n * N2];
 #pragma unroll
                 for (int j = 0; j < kDft2Q1; ++j) {
-                    t[j] = step(t[j], by[j]);
                     const double2 w = twiddle(t[j]);
-                    re[j] = fma(e, w.x, re[j]);
-                    im[j] = fma(o, w.y, im[j]);
+                    t[j] = step(t[j], by[j]);
+                    re[j] = fma(u, w.x, re[j]);
+                    im[j] = fma(u, w.y, im[j]);
                 }
             }
             if (!live) continue;
@@ -568,11 +569,11 @@ __global__ __launch_bounds__(256) void k_window_dft2(FftArgs args) {
                 const int q = q0 + j;
                 if (2 * q > N1) break;
                 const double2 w = a.tw64[n2 * q];        // n2 k1 < N
-                y[q * (N2 + 1)] = make_float2((float)(re[j] * w.x - im[j] * w.y), (float)(re[j] * w.y + im[j] * w.x));
+                y[q * (N2 + 1)] = make_float2((float)fma(re[j], w.x, -(im[j] * w.y)), (float)fma(im[j], w.x, re[j] * w.y));
                 if (q == 0 || 2 * q == N1) continue;
                 const double2 z = a.tw64[n2 * (N1 - q)];
                 y[(N1 - q) * (N2 + 1)] =
-                    make_float2((float)(re[j] * z.x + im[j] * z.y), (float)(re[j] * z.y - im[j] * z.x));
+                    make_float2((float)fma(re[j], z.x, im[j] * z.y), (float)fma(-im[j], z.x, re[j] * z.y));
             }
         }
     }
@@ -704,8 +705,8 @@ hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
         const int n2 = c.dft_n / c.dft_n1;
         if (n2 * c.dft_n1 != c.dft_n || c.dft_n1 > n2) return hipErrorInvalidValue;
         if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
-        // A quarter of the lanes with rows: 24 rows take 76 us against 156 (2^22
-        // samples, N = 1016 = 8 x 127, three frames) and 87 against 154 (N = 3336 =
+        // A quarter of the lanes with rows: 24 rows take 83 us against 156 (2^22
+        // samples, N = 1016 = 8 x 127, three frames) and 95 against 154 (N = 3336 =
         // 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against
         // 303 (N = 4072 = 8 x 509).
         const int F = dft2_frames(c.dft_n, c.dft_n1);
