@@ -625,6 +625,14 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                     if (a.blocks == 0) a.p4 = sg.op4;
                 }
             };
+            // Finalize items of a grid spectrum: sub-blocks of its tiles, without
+            // those that the moment kernels finalize (see FinalizeArgs.direct).
+            const bool direct_tiles = !slots && !per_chunk && B.stride == 1;
+            auto grid_items = [&](const ps::Seg& sg, int64_t points) {
+                const ps::Sched sc{sg.n_tiles, sg.n_chunks, sg.blocks};
+                const int64_t tiles = !direct_tiles ? sg.n_tiles : sg.n_chunks == 1 ? 0 : sc.R();
+                return tiles * (points / 256);
+            };
             ps::Seg base{};
             // the record's chunk 0 (per-chunk schedule: the class block holds the current chunk)
             base.coef = (int64_t)(k.coef_off / sizeof(float2)) + (per_chunk ? 0 : q.frame0 * K);
@@ -690,7 +698,7 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 sg.sym = sym;
                 sg.ncomp = 4;
                 G.s3.add(sg, sg.blocks);
-                finalize(G.f3, fin3, i, sg, (int64_t)sg.n_tiles * (TT / 256));
+                if (grid_items(sg, TT) || !direct_tiles) finalize(G.f3, fin3, i, sg, grid_items(sg, TT));
             }
             std::vector<int64_t> part4(p->n4());
             for (int i = 0; i < p->n4(); ++i) {
@@ -730,10 +738,15 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 sg.sym = sym;
                 if (first) {
                     ps::Seg ms = sg;
-                    if (pair >= 0) ms.part2 = part4[pair];
+                    if (pair >= 0) {
+                        ms.part2 = part4[pair];
+                        ms.p4 = (int64_t)(uintptr_t)(o && o->d_s4 ? o->d_s4 + 2 * pair * nf2 : nullptr);
+                        ms.p4_cs = (int64_t)(uintptr_t)(o && o->d_s4_err ? o->d_s4_err + 2 * pair * nf2 : nullptr);
+                    }
                     (single ? G.s4s : G.s4x).add(ms, ms.blocks);
                 }
-                finalize(G.f4, fin4, i, sg, (int64_t)sg.n_tiles * ((single ? TT : TX) / 256));
+                if (grid_items(sg, single ? TT : TX) || !direct_tiles)
+                    finalize(G.f4, fin4, i, sg, grid_items(sg, single ? TT : TX));
             }
         }
     }
@@ -1365,6 +1378,7 @@ ps::BatchArgs batch_args(const ps_plan_s* p, const Batch& B, const SegTable& t, 
                          int per_chunk, int win_lo, int win_hi, int accumulate, int finalized) {
     ps::BatchArgs a{};
     a.finalized = finalized;
+    a.direct = finalized && B.stride == 1;
     a.segs = reinterpret_cast<const ps::Seg*>(tab + t.dev_off);
     a.n_segs = (int)t.v.size();
     a.n_items = t.n_items;
@@ -1435,6 +1449,7 @@ ps_status launch_finalize(ps_plan_t p, const Batch& B, const Group& G, char* ws,
     f.tab[ps::kFinS4] = fin_table(G.f4, tab);
     f.part = reinterpret_cast<const double*>(ws + B.off_part);
     f.ws = reinterpret_cast<const float2*>(ws);
+    f.direct = B.stride == 1 && p->schedule != PS_SCHED_PER_CHUNK;
     f.s1 = p->has(1) ? reinterpret_cast<const float2*>(ws + B.off_s1) : nullptr;
     f.s1_cs = B.chunks_tot;
     PS_HIP(ps::launch_finalize(f, st));

@@ -170,8 +170,10 @@ __device__ __forceinline__ void finalize_tile(const FinalizeArgs& p, const Final
     const int TT = E * E;
     const int sub = E / 16, per_tile = sub * sub;
     const int64_t local = x - sg.item0;
-    const int tile = (int)(local / per_tile);
-    const int sb = (int)(local - (int64_t)tile * per_tile);
+    const int64_t nth = local / per_tile;
+    const int sb = (int)(local - nth * per_tile);
+    // (direct: the first T1 tiles are whole, their blocks are not launched)
+    const int tile = (int)(nth + (p.direct ? Sched{sg.n_tiles, sg.n_chunks, sg.blocks}.T1() : 0));
     const int2 t = tile_at(sg.tile_tab, tile);
     const int kb = t.x * E + 16 * (sb / sub), lb = t.y * E + 16 * (sb % sub);   // sub-block origin
     const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
@@ -188,6 +190,7 @@ __device__ __forceinline__ void finalize_tile(const FinalizeArgs& p, const Final
         const double np = (double)W;
         int64_t s0 = 0, ns = 0;
         if (W > 0) slot_range(Sched{sg.n_tiles, W, set ? sg.blocks2 : sg.blocks}, tile, s0, ns);
+        if (p.direct && ns == 1) return;        // (uniform; interlaced sets are never direct)
         double s[4] = {0, 0, 0, 0};
         const double* q = p.part + (set ? sg.part2 : sg.part) + s0 * ncomp * TT;
         if (W == 1) {       // one slot, no squares in it

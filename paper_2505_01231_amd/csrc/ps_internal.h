@@ -215,6 +215,8 @@ struct Seg {
     // start), op4_cs = 1: the segment takes those in place of coefficients.
     int64_t op4, op4_cs;
     // and its (column sum of P, scale s^2) pairs (double offset), channel stride.
+    // Cross-channel S4 stage with part2: the addresses of the second
+    // combination's spectrum and error bar.
     // S2 finalize with blocks == 0 (no partial sums: the chunk terms themselves
     // are added): p4 the shifted frame set's chunk terms.
     int64_t p4, p4_cs;
@@ -260,6 +262,7 @@ struct BatchArgs {
     // leaves the sums of its squares (the later half of the components)
     // unwritten, and the finalize does not read them.
     int finalized;
+    int direct;             // pieces that cover a tile whole write the spectrum (FinalizeArgs.direct)
     // S4 kernels form v = M4 - gamma (p_k p_l + |Q|^2 + |R|^2) in FP64:
     // gamma = (m-1)/(m(m+1)) for the k-statistic, 1/m for the natural estimator
     double gamma;
@@ -298,6 +301,7 @@ struct FinalizeArgs {
     FinalizeTable tab[4];   // in launch order
     const double* part;
     const float2* ws;       // workspace start (S2's chunk terms)
+    int direct;             // tiles of one slot were written by the moment kernels
     const float2* s1;       // per-chunk means of a_0, [C][s1_cs] (S1 only)
     int64_t s1_cs;
 };

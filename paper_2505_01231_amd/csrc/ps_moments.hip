@@ -49,6 +49,7 @@ struct Item {
     int k0, l0;
     int ch[4];
     double* part;           // partial-sum slot of the piece
+    bool whole;             // every chunk of the tile: the piece is written as spectrum and error bar
 };
 
 // Coefficients of the item's record: chunk c, frame f, column k of channel ch
@@ -132,10 +133,72 @@ __device__ __forceinline__ bool next_item(const BatchArgs& b, Block& bk, Item& i
         it.l0 = 0;
         it.part = b.part + s.part + slot * NCOMP * 256;
     }
+    it.whole = EDGE > 0 && b.direct && c0 == 0 && c1 == bk.sc.W;
 #pragma unroll
     for (int q = 0; q < 4; ++q) it.ch[q] = s.ch[q];
     return true;
 }
+
+// Mean and error bar of the grid points of a whole tile, as the finalize forms
+// them, written where the moment kernel has the sums: no partial sums (64 or 32
+// bytes a point) are written and read back.  x / np by the reciprocal and one
+// correction, which rounds as the division does (infinities and NaN pass
+// through).  Points with k < l of a symmetric spectrum are also written at
+// (l, k): 64-byte runs of four rows, which the L2 joins.
+struct Emit {
+    double np, inv, scale;
+    double *out, *err;
+    int Nf;
+    bool sym;
+
+    __device__ __forceinline__ Emit(ConstSeg& s, double* o, double* e)
+        : np(s.n_chunks), inv(1.0 / s.n_chunks), scale(s.scale), out(o), err(e), Nf(s.Nf), sym(s.sym) {}
+    __device__ __forceinline__ double over_np(double x) const {
+        const double q = x * inv, r = fma(fma(-q, np, x), inv, q);
+        return r == r ? r : q;
+    }
+    __device__ __forceinline__ void mean_sigma(double s, double s2, double& mean, double& sigma) const {
+        const double mu = over_np(s);
+        mean = scale * mu;
+        if (np < 2.0) {
+            sigma = __longlong_as_double(0x7ff8000000000000LL);
+            return;
+        }
+        const double var = np / (np - 1.0) * (over_np(s2) - mu * mu);
+        sigma = fabs(scale) * sqrt(over_np(fmax(var, 0.0)));
+    }
+    __device__ __forceinline__ void put(int k, int l, double mr, double mi, double sr, double si) const {
+        if (k >= Nf || l >= Nf || (sym && k > l)) return;
+        const int64_t a = 2 * ((int64_t)k * Nf + l), b = 2 * ((int64_t)l * Nf + k);
+        const bool twice = sym && k < l;
+        if (out) {
+            out[a] = mr, out[a + 1] = mi;
+            if (twice) out[b] = mr, out[b + 1] = mi;
+        }
+        if (err) {
+            err[a] = sr, err[a + 1] = si;
+            if (twice) err[b] = sr, err[b + 1] = si;
+        }
+    }
+    __device__ __forceinline__ void operator()(int k, int l, const double (&a)[4]) const {
+        double mr, sr, mi, si;
+        mean_sigma(a[0], a[2], mr, sr);
+        mean_sigma(a[1], a[3], mi, si);
+        put(k, l, mr, mi, sr, si);
+    }
+    // one point of a real spectrum, not mirrored
+    __device__ __forceinline__ void put_one(int k, int l, bool on, double m, double sg) const {
+        if (!on || k >= Nf || l >= Nf) return;
+        const int64_t a = 2 * ((int64_t)k * Nf + l);
+        if (out) out[a] = m, out[a + 1] = 0.0;
+        if (err) err[a] = sg, err[a + 1] = np < 2.0 ? sg : 0.0;
+    }
+    __device__ __forceinline__ void operator()(int k, int l, const double (&a)[2]) const {     // real
+        double m, sg;
+        mean_sigma(a[0], a[1], m, sg);
+        put(k, l, m, 0.0, sg, np < 2.0 ? sg : 0.0);
+    }
+};
 
 // ------------------------------------------------------------------ S2
 // For one channel, chunks of up to kS2Regs frames are loaded whole before
@@ -227,7 +290,7 @@ constexpr int kS3Threads = 256;
 
 // One piece of work (a tile and a range of its chunks) of k_s3.
 template <int FB, bool DIAG>
-__device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, const Item& it, float2 (*sA)[kTile],
+__device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, ConstSeg& sg, const Item& it, float2 (*sA)[kTile],
                                         float2 (*sB)[kTile], float2 (*sC)[2 * kTile]) {
     const int c0 = it.c0, c1 = it.c1;
     const int k0 = it.k0, l0 = it.l0;
@@ -323,6 +386,13 @@ __device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, const
         }
     }
 
+    if (it.whole) {
+        const Emit emit(sg, sg.out, sg.err);
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (!DIAG || (q >> 2) <= (q & 3)) emit(k0 + ti + 16 * (q >> 2), l0 + tj + 16 * (q & 3), acc[q]);
+        return;
+    }
     // (A piece's 128 KB: 10^6 samples at N_f = 200 are 512 pieces of two chunks.
     // The end after half the components also keeps the compiler from forming
     // every address at once, which spilled 91 registers per piece: 33 -> 22 us
@@ -356,8 +426,8 @@ __global__ __launch_bounds__(kS3Threads, 2) void k_s3(BatchArgs p) {
     if (!resolve_block(p, bk, v)) return;
     Item it;
     while (next_item<kTile, 4>(p, bk, it)) {
-        if (bk.s->tiles == kSym64 && it.k0 == it.l0) s3_item<FB, true>(p, v, it, sA, sB, sC);
-        else s3_item<FB, false>(p, v, it, sA, sB, sC);
+        if (bk.s->tiles == kSym64 && it.k0 == it.l0) s3_item<FB, true>(p, v, *bk.s, it, sA, sB, sC);
+        else s3_item<FB, false>(p, v, *bk.s, it, sA, sB, sC);
     }
 }
 
@@ -386,6 +456,40 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// A wave's 32 x 32 points of a whole tile (real spectrum): register r of lane
+// (kh, r32) is the point (k0 + 8 (r / 4) + 4 kh + r % 4, l0 + r32).  The mirror
+// (l, k) goes through wave-private LDS, eight rows at a time, so that it is
+// written in 128-byte runs (a lane's own points would be 16-byte writes 16 N_f
+// bytes apart: 345 us against 204 for 409 records of one chunk at N_f = 256).
+struct Mirror {
+    double v[2][32][9];
+};
+
+__device__ __forceinline__ void emit_quadrant(const Emit& e, Mirror& m, int k0, int l0, int lane,
+                                              const double (&acc)[16][2]) {
+    const int r32 = lane & 31, kh = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int q = 4 * kh + i, k = k0 + 8 * j + q, l = l0 + r32;
+            double mean, sigma;
+            e.mean_sigma(acc[4 * j + i][0], acc[4 * j + i][1], mean, sigma);
+            e.put_one(k, l, !e.sym || k <= l, mean, sigma);
+            m.v[0][r32][q] = mean;
+            m.v[1][r32][q] = sigma;
+        }
+        if (!e.sym) continue;
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = 8 * i + (lane >> 3), q = lane & 7, k = k0 + 8 * j + q, l = l0 + c;
+            e.put_one(l, k, k < l, m.v[0][c][q], m.v[1][c][q]);
+        }
+        wave_lds_fence();
+    }
 }
 
 // ------------------------------------------------------------------ S4, one channel, FP32
@@ -417,6 +521,7 @@ template <bool ONE_BATCH>
 __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
     __shared__ float2 sm[2][2][kS4FFrames][kTile];      // [buffer][side k, l][frame][column]
     __shared__ double ps[4][64];                        // per wave: -gamma p_k (32 rows), p_l (32 columns)
+    __shared__ Mirror mirror[4];
 
     Block bk;
     View v;
@@ -517,6 +622,10 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
         }
     }
 
+    if (it.whole) {
+        emit_quadrant(Emit(*bk.s, bk.s->out, bk.s->err), mirror[w], it.k0 + 32 * (w >> 1), it.l0 + 32 * (w & 1), lane, acc);
+        continue;
+    }
     double* o = it.part;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -632,6 +741,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
     __shared__ __attribute__((aligned(16))) uint32_t opK[3 * kTile][kOpDw];
     __shared__ __attribute__((aligned(16))) uint32_t opL[3 * kTile][kOpDw];
     __shared__ double psum[2][kTile];          // -gamma p_k (k side), p_l (l side)
+    __shared__ Mirror mirror[4];
 
     Block bk;
     View v;
@@ -754,6 +864,10 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
         }
     }
 
+    if (it.whole) {
+        emit_quadrant(Emit(*bk.s, bk.s->out, bk.s->err), mirror[w], it.k0 + 32 * (w >> 1), it.l0 + 32 * (w & 1), lane, acc);
+        continue;
+    }
     double* o = it.part;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -950,6 +1064,14 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16(BatchArgs p) {
         }
     }
 
+    if (it.whole) {
+        const Emit emit(*bk.s, bk.s->out, bk.s->err);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int lb = 0; lb < 4; ++lb) emit(it.k0 + w * 16 + 4 * lg + e, it.l0 + lb * 16 + li, acc[lb][e]);
+        continue;
+    }
     double* o = it.part;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1112,6 +1234,7 @@ struct S4Stage {
 
 __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p) {
     __shared__ __attribute__((aligned(16))) S4Stage stage[kS4Stages];
+    __shared__ Mirror mirror[4];
 
     Block bk;
     View v;
@@ -1289,6 +1412,10 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
         if (++c >= c1) break;
     }
 
+    if (it.whole) {
+        emit_quadrant(Emit(*bk.s, bk.s->out, bk.s->err), mirror[w], it.k0 + 32 * (w >> 1), it.l0 + 32 * (w & 1), lane, acc);
+        continue;
+    }
     double* o = it.part;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -1468,6 +1595,12 @@ __global__ __launch_bounds__(kS4XThreads, 3) void k_s4_cross_f32(BatchArgs p) {
         }
     }
 
+    if (it.whole) {
+        const Emit emit(*bk.s, bk.s->out, bk.s->err);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) emit(it.k0 + 16 * (w >> 1) + 4 * g + q, it.l0 + rowB, acc[q]);
+        continue;
+    }
     constexpr int TT = kTileX * kTileX;
     double* o = it.part;
 #pragma unroll
@@ -1595,7 +1728,7 @@ __device__ __forceinline__ void cross_combine(double (&acc)[4], double gamma, Cp
 // One piece of work.  ONE_BATCH: every chunk fits one frame batch (m <= 10), so
 // each batch starts and ends a chunk (compile-time).
 template <int FORM, bool ONE_BATCH>
-__device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v, const Item& it, double* part_pair,
+__device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v, ConstSeg& sg, const Item& it, double* part_pair,
                                               CrossLds& sm) {
     constexpr bool kAB = FORM == kXSameAB || FORM == kXSameBoth, kCD = FORM == kXSameCD || FORM == kXSameBoth;
     constexpr bool kPair = FORM == kXPair;
@@ -1752,6 +1885,15 @@ __device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v,
         }
     }
 
+    if (it.whole) {
+#pragma unroll
+        for (int out = 0; out < kOut; ++out) {
+            const Emit emit(sg, out ? reinterpret_cast<double*>(sg.p4) : sg.out, out ? reinterpret_cast<double*>(sg.p4_cs) : sg.err);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) emit(it.k0 + 16 * (w >> 1) + 4 * lg + e, it.l0 + rowB, acc[out][e]);
+        }
+        return;
+    }
     constexpr int TT = kTileX * kTileX;
 #pragma unroll
     for (int out = 0; out < kOut; ++out) {
@@ -1787,11 +1929,11 @@ __global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) 
     const int64_t pair = bk.s->part2 ? bk.s->part2 - bk.s->part : 0;
     Item it;
     while (next_item<kTileX, 4>(p, bk, it)) {
-        if (pair) s4_cross_item<kXPair, ONE_BATCH>(p, v, it, it.part + pair, sm);
-        else if (ab && cd) s4_cross_item<kXSameBoth, ONE_BATCH>(p, v, it, nullptr, sm);
-        else if (ab) s4_cross_item<kXSameAB, ONE_BATCH>(p, v, it, nullptr, sm);
-        else if (cd) s4_cross_item<kXSameCD, ONE_BATCH>(p, v, it, nullptr, sm);
-        else s4_cross_item<kXGeneral, ONE_BATCH>(p, v, it, nullptr, sm);
+        if (pair) s4_cross_item<kXPair, ONE_BATCH>(p, v, *bk.s, it, it.part + pair, sm);
+        else if (ab && cd) s4_cross_item<kXSameBoth, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
+        else if (ab) s4_cross_item<kXSameAB, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
+        else if (cd) s4_cross_item<kXSameCD, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
+        else s4_cross_item<kXGeneral, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
     }
 }
 
