@@ -176,6 +176,7 @@ __device__ __forceinline__ void finalize_tile(const FinalizeArgs& p, const Final
     const int tile = (int)(nth + (p.direct ? Sched{sg.n_tiles, sg.n_chunks, sg.blocks}.T1() : 0));
     const int2 t = tile_at(sg.tile_tab, tile);
     const int kb = t.x * E + 16 * (sb / sub), lb = t.y * E + 16 * (sb % sub);   // sub-block origin
+    if (kb >= sg.Nf || lb >= sg.Nf || (sg.sym && kb > lb)) return;     // no point to write
     const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
     const int ncomp = sg.ncomp;
     const bool two = sg.n_chunks2 > 0;

@@ -64,6 +64,19 @@ struct View {
     int64_t cs, off;
     int K, m, Nf, col0, col3;
     bool lone;              // one chunk: its squares are not wanted (no error bar)
+    // Only the 16 x 16 sub-blocks that the finalize reads are wanted: those with
+    // points of the grid, of a symmetric spectrum none below the diagonal
+    // (N_f = 200: 91 of the 160 in its ten tiles).  A running accumulation adds
+    // every slot whole.
+    bool trim, sym;
+    __device__ __forceinline__ bool wanted(int k, int l) const {
+        const int kb = k & ~15, lb = l & ~15;
+        return !trim || (kb < Nf && lb < Nf && !(sym && kb > lb));
+    }
+    // no sub-block of the n x n points from (k, l), on n's grid, is wanted
+    __device__ __forceinline__ bool unwanted(int k, int l) const {
+        return trim && (k >= Nf || l >= Nf || (sym && k > l));
+    }
 };
 
 __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, View& v) {
@@ -94,6 +107,8 @@ __device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, Vie
     v.m = b.m;
     v.Nf = s.Nf;
     v.lone = b.finalized && s.n_chunks == 1;
+    v.trim = b.finalized;
+    v.sym = s.sym;
     return true;
 }
 
@@ -137,6 +152,14 @@ __device__ __forceinline__ bool next_item(const BatchArgs& b, Block& bk, Item& i
 #pragma unroll
     for (int q = 0; q < 4; ++q) it.ch[q] = s.ch[q];
     return true;
+}
+
+// A lane's offset in a piece's slot, formed here: the offsets of its points and
+// components are otherwise kept over the loop over pieces, which spilled 90
+// registers of k_s3 (33 -> 22 us for 512 pieces of two chunks).
+__device__ __forceinline__ int formed_here(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 // Mean and error bar of the grid points of a whole tile, as the finalize forms
@@ -393,17 +416,14 @@ __device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, Const
             if (!DIAG || (q >> 2) <= (q & 3)) emit(k0 + ti + 16 * (q >> 2), l0 + tj + 16 * (q & 3), acc[q]);
         return;
     }
-    // (A piece's 128 KB: 10^6 samples at N_f = 200 are 512 pieces of two chunks.
-    // The end after half the components also keeps the compiler from forming
-    // every address at once, which spilled 91 registers per piece: 33 -> 22 us
-    // there, and 175 -> 81 for 409 records of one chunk at N_f = 256, where the
-    // squares of one chunk are 0.27 GB.)
     double* o = it.part;
+    const int at = formed_here(ti * kTile + tj);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const int idx = (ti + 16 * u) * kTile + tj + 16 * w;
+            const int idx = at + 16 * u * kTile + 16 * w;
+            if (!v.wanted(k0 + 16 * u, l0 + 16 * w)) continue;
 #pragma unroll
             for (int comp = 0; comp < 4; ++comp) {
                 if (comp >= 2 && v.lone) break;
@@ -583,6 +603,7 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
             fb += kS4FFrames;
         }
         if (b + 1 < n_batches) fetch(c, fb);
+        if (v.unwanted(it.k0 + 32 * (w >> 1), it.l0 + 32 * (w & 1))) continue;     // (this wave's quadrant)
 
         if (first) {
             pacc = 0.f;
@@ -627,9 +648,11 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
         continue;
     }
     double* o = it.part;
+    const int at = formed_here((32 * (w >> 1) + 4 * kh) * kTile + 32 * (w & 1) + r32);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + rowL;
+        const int idx = at + (8 * (r >> 2) + (r & 3)) * kTile;
+        if (!v.wanted(it.k0 + 32 * (w >> 1) + 8 * (r >> 2), it.l0 + 32 * (w & 1) + r32)) continue;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
             if (comp >= 1 && v.lone) break;
@@ -784,7 +807,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
     for (int r = 0; r < 16; ++r) acc[r][0] = acc[r][1] = 0.0;
 
     constexpr int kSlots = kMfmaFrames / 2;       // frame slots of this thread: half + 2j
-    const int per_chunk = (v.m + kMfmaFrames - 1) / kMfmaFrames;
+    const int per_chunk = ONE_BATCH ? 1 : (v.m + kMfmaFrames - 1) / kMfmaFrames;
     const int n_batches = (c1 - c0) * per_chunk;
     float2 pre[kSlots];
     auto fetch = [&](int b) {
@@ -814,6 +837,10 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
             if (half == 0) psum[side][col] = side == 0 ? -gamma * (double)tot : (double)tot;
         }
         lds_barrier();
+        if (v.unwanted(k0 + 32 * (w >> 1), l0 + 32 * (w & 1))) {       // (this wave's quadrant)
+            if (b + 1 < n_batches) fetch(b + 1);
+            continue;
+        }
         // Four K steps of 16 slots (the scheduling barrier keeps each step's
         // operand reads next to its contractions: fewer live registers).  The
         // wave runs them at raised priority, so that the matrix pipe is fed
@@ -869,9 +896,11 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
         continue;
     }
     double* o = it.part;
+    const int at = formed_here((32 * (w >> 1) + 4 * kh) * kTile + 32 * (w & 1) + r32);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + 32 * (w & 1) + r32;
+        const int idx = at + (8 * (r >> 2) + (r & 3)) * kTile;
+        if (!v.wanted(it.k0 + 32 * (w >> 1) + 8 * (r >> 2), it.l0 + 32 * (w & 1) + r32)) continue;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
             if (comp >= 1 && v.lone) break;
@@ -1073,11 +1102,13 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16(BatchArgs p) {
         continue;
     }
     double* o = it.part;
+    const int at = formed_here((w * 16 + 4 * lg) * kTile + li);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
 #pragma unroll
         for (int lb = 0; lb < 4; ++lb) {
-            const int idx = (w * 16 + 4 * lg + e) * kTile + lb * 16 + li;
+            const int idx = at + e * kTile + lb * 16;
+            if (!v.wanted(it.k0 + w * 16, it.l0 + lb * 16)) continue;
 #pragma unroll
             for (int comp = 0; comp < 2; ++comp) {
                 if (comp >= 1 && v.lone) break;
@@ -1312,6 +1343,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r][0] = acc[r][1] = 0.0;
 
+    const bool idle = v.unwanted(it.k0 + 32 * (w >> 1), it.l0 + 32 * (w & 1));      // (this wave's quadrant)
     // Chunk c from stage B (a compile-time index, so that every LDS read
     // offset is an immediate).
     auto step = [&](auto B, int c) {
@@ -1325,6 +1357,7 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
         __builtin_amdgcn_s_waitcnt(0x0075);                            // vmcnt(5) lgkmcnt(0)
         lds_sync();
         copy_chunk(b == 0 ? kS4Stages - 1 : b - 1, c + kS4Stages - 1);
+        if (idle) return;
 
         u32x4_v op[12];
         read_lds_ops<so, so + kValBytes, so + 2 * kValBytes>(aK0, aL0, aK1, aL1, op);
@@ -1417,9 +1450,11 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
         continue;
     }
     double* o = it.part;
+    const int at = formed_here((32 * (w >> 1) + 4 * kh) * kTile + 32 * (w & 1) + r32);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int idx = (32 * (w >> 1) + 8 * (r >> 2) + 4 * kh + (r & 3)) * kTile + 32 * (w & 1) + r32;
+        const int idx = at + (8 * (r >> 2) + (r & 3)) * kTile;
+        if (!v.wanted(it.k0 + 32 * (w >> 1) + 8 * (r >> 2), it.l0 + 32 * (w & 1) + r32)) continue;
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
             if (comp >= 1 && v.lone) break;
@@ -1603,9 +1638,11 @@ __global__ __launch_bounds__(kS4XThreads, 3) void k_s4_cross_f32(BatchArgs p) {
     }
     constexpr int TT = kTileX * kTileX;
     double* o = it.part;
+    const int at = formed_here((16 * (w >> 1) + 4 * g) * kTileX + rowB);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int idx = (16 * (w >> 1) + 4 * g + q) * kTileX + rowB;
+        const int idx = at + q * kTileX;
+        if (!v.wanted(it.k0 + 16 * (w >> 1), it.l0 + 16 * (w & 1))) continue;
 #pragma unroll
         for (int comp = 0; comp < 4; ++comp) {
             if (comp >= 2 && v.lone) break;
@@ -1901,6 +1938,7 @@ __device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v,
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int idx = (16 * (w >> 1) + 4 * lg + e) * kTileX + rowB;
+            if (!v.wanted(it.k0 + 16 * (w >> 1), it.l0 + 16 * (w & 1))) continue;
 #pragma unroll
             for (int comp = 0; comp < 4; ++comp) {
                 if (comp >= 2 && v.lone) break;
