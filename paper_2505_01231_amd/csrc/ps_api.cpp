@@ -194,7 +194,9 @@ struct ps_plan_s {
     int s4_pair(int i, bool& first) const {
         const int8_t* q = &c4[4 * i];
         first = true;
-        if (precision != PS_PREC_BF16X3 || s4_shift != 0 || q[0] == q[1] || q[2] == q[3] || s4_sym(i)) return -1;
+        // (chunks of several frame batches: the pair form's loop does not fit the registers)
+        if (precision != PS_PREC_BF16X3 || s4_shift != 0 || m > ps::kPairFrames) return -1;
+        if (q[0] == q[1] || q[2] == q[3] || s4_sym(i)) return -1;
         // the k-th combination (a, b, c, d) goes with the k-th (a, b, d, c)
         int nth = 0, same = 0;
         auto is = [&](int j, int c, int d) {

@@ -269,6 +269,10 @@ struct BatchArgs {
     int s4_shift;           // S4 planes: a, d at +q columns, b, c at -q (cross-channel kernels only)
     int s3_fb;              // S3 frames per LDS batch (10, 11 or 16); 0: chosen by the rows per chunk
 };
+// Longest chunks whose cross-channel S4 combinations (BF16 x 3) are formed in
+// pairs: one frame batch.  With several the pair form spills in its loop (three
+// channels, m = 12, 2^21 samples: 2720 us, every combination alone 1630).
+constexpr int kPairFrames = 10;
 hipError_t launch_s2(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s3(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s);

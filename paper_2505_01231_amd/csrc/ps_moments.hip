@@ -699,6 +699,7 @@ typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kMfmaFrames = 10;      // frames per operand batch: 6 x 10 = 60 <= 64 slots
+static_assert(kPairFrames <= kMfmaFrames, "pairs are formed within one frame batch");
 constexpr int kOpDw = 36;            // 32-bit words per LDS operand row (144 B; 32 used)
 constexpr int kS4MThreads = 256;
 
@@ -1967,7 +1968,7 @@ __global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) 
     const int64_t pair = bk.s->part2 ? bk.s->part2 - bk.s->part : 0;
     Item it;
     while (next_item<kTileX, 4>(p, bk, it)) {
-        if (pair) s4_cross_item<kXPair, ONE_BATCH>(p, v, *bk.s, it, it.part + pair, sm);
+        if (ONE_BATCH && pair) s4_cross_item<ONE_BATCH ? kXPair : kXGeneral, ONE_BATCH>(p, v, *bk.s, it, it.part + pair, sm);
         else if (ab && cd) s4_cross_item<kXSameBoth, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
         else if (ab) s4_cross_item<kXSameAB, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
         else if (cd) s4_cross_item<kXSameCD, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
