@@ -1411,27 +1411,41 @@ ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, 
         StageTimer t(p, st, 2);
         PS_HIP(ps::launch_s2(batch_args(p, B, G.s2, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized), st));
     }
-    if (G.s3.n_items) {
-        StageTimer t(p, st, 3);
-        ps::BatchArgs a = batch_args(p, B, G.s3, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized);
-        // the c3^(opt) rows: m shifted frames and one mean row per chunk
-        // (the segments point at their blocks)
-        if (p->c3opt()) a.m = p->m + 1;
-        PS_HIP(ps::launch_s3(a, st));
-    }
-    if (G.s4s.n_items) {
-        StageTimer t(p, st, 4);
+    auto s4_args = [&] {
         ps::BatchArgs a = batch_args(p, B, G.s4s, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized);
         if (p->s4_pre) {                // operands split by the centring pass
             a.op4 = reinterpret_cast<const uint32_t*>(ws);
             a.p4 = reinterpret_cast<const double*>(ws);
         }
-        if (p->precision == PS_PREC_FP32) {
-            PS_HIP(ps::launch_s4_single(a, st));
-        } else if (p->precision == PS_PREC_BF16X3) {
-            PS_HIP(ps::launch_s4_mfma(a, st));
-        } else {
-            PS_HIP(ps::launch_s4_mfma_f16(a, st));
+        return a;
+    };
+    // S3 and the single-channel S4 in one launch (stage timing keeps them apart)
+    const bool s4_merges = p->precision != PS_PREC_FP16X2S || p->s4_pre;
+    if (G.s3.n_items && G.s4s.n_items && !p->prof && !p->c3opt() && p->m <= ps::kFrameBatchSmall &&
+        (p->s3_fb == 0 || p->s3_fb == ps::kFrameBatchSmall) && s4_merges) {
+        const ps::S4Kind kind = p->precision == PS_PREC_FP32     ? ps::kS4F32
+                                : p->precision == PS_PREC_BF16X3 ? ps::kS4Bf16
+                                                                 : ps::kS4Pre;
+        PS_HIP(ps::launch_s3_s4(batch_args(p, B, G.s3, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized),
+                                s4_args(), kind, st));
+    } else {
+        if (G.s3.n_items) {
+            StageTimer t(p, st, 3);
+            ps::BatchArgs a = batch_args(p, B, G.s3, ws, tab, per_chunk, win_lo, win_hi, accumulate, finalized);
+            // the c3^(opt) rows: m shifted frames and one mean row per chunk
+            // (the segments point at their blocks)
+            if (p->c3opt()) a.m = p->m + 1;
+            PS_HIP(ps::launch_s3(a, st));
+        }
+        if (G.s4s.n_items) {
+            StageTimer t(p, st, 4);
+            if (p->precision == PS_PREC_FP32) {
+                PS_HIP(ps::launch_s4_single(s4_args(), st));
+            } else if (p->precision == PS_PREC_BF16X3) {
+                PS_HIP(ps::launch_s4_mfma(s4_args(), st));
+            } else {
+                PS_HIP(ps::launch_s4_mfma_f16(s4_args(), st));
+            }
         }
     }
     if (G.s4x.n_items) {

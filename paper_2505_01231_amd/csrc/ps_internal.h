@@ -275,6 +275,9 @@ struct BatchArgs {
 constexpr int kPairFrames = 10;
 hipError_t launch_s2(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s3(const BatchArgs& a, hipStream_t s);
+// S3 and the single-channel S4 in one launch: up to 10 rows per chunk in both.
+enum S4Kind { kS4F32, kS4Bf16, kS4Pre };
+hipError_t launch_s3_s4(const BatchArgs& s3, const BatchArgs& s4, S4Kind kind, hipStream_t s);
 hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s4_mfma(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s4_mfma_f16(const BatchArgs& a, hipStream_t s);

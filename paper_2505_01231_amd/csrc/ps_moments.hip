@@ -79,9 +79,9 @@ struct View {
     }
 };
 
-__device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, View& v) {
+__device__ __forceinline__ bool resolve_block(const BatchArgs& b, Block& bk, View& v, unsigned block = blockIdx.x) {
     const int64_t per_xcd = (b.n_items + 7) >> 3;
-    const int64_t x = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int64_t x = (int64_t)(block & 7) * per_xcd + (block >> 3);
     if (x >= b.n_items) return false;
     ConstSeg& s = *find_seg(b.segs, b.n_segs, x);
     bk.s = &s;
@@ -436,19 +436,26 @@ __device__ __forceinline__ void s3_item(const BatchArgs& p, const View& v, Const
 }
 
 template <int FB>
-__global__ __launch_bounds__(kS3Threads, 2) void k_s3(BatchArgs p) {
-    __shared__ float2 sA[FB][kTile];
-    __shared__ float2 sB[FB][kTile];
-    __shared__ float2 sC[FB][2 * kTile];
+struct S3Lds {
+    float2 a[FB][kTile], b[FB][kTile], c[FB][2 * kTile];
+};
 
+template <int FB>
+__device__ __forceinline__ void s3_block(const BatchArgs& p, unsigned block, S3Lds<FB>& lds) {
     Block bk;
     View v;
-    if (!resolve_block(p, bk, v)) return;
+    if (!resolve_block(p, bk, v, block)) return;
     Item it;
     while (next_item<kTile, 4>(p, bk, it)) {
-        if (bk.s->tiles == kSym64 && it.k0 == it.l0) s3_item<FB, true>(p, v, *bk.s, it, sA, sB, sC);
-        else s3_item<FB, false>(p, v, *bk.s, it, sA, sB, sC);
+        if (bk.s->tiles == kSym64 && it.k0 == it.l0) s3_item<FB, true>(p, v, *bk.s, it, lds.a, lds.b, lds.c);
+        else s3_item<FB, false>(p, v, *bk.s, it, lds.a, lds.b, lds.c);
     }
+}
+
+template <int FB>
+__global__ __launch_bounds__(kS3Threads, 2) void k_s3(BatchArgs p) {
+    __shared__ S3Lds<FB> lds;
+    s3_block<FB>(p, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------ FP32 matrix cores
@@ -537,15 +544,21 @@ constexpr int kS4FFrames = 10;
 constexpr int kS4Threads = 256;
 
 // ONE_BATCH: every chunk fits one frame batch (m <= 10).
+struct S4F32Lds {
+    float2 sm[2][2][kS4FFrames][kTile];     // [buffer][side k, l][frame][column]
+    double ps[4][64];                       // per wave: -gamma p_k (32 rows), p_l (32 columns)
+    Mirror mirror[4];
+};
+
 template <bool ONE_BATCH>
-__global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
-    __shared__ float2 sm[2][2][kS4FFrames][kTile];      // [buffer][side k, l][frame][column]
-    __shared__ double ps[4][64];                        // per wave: -gamma p_k (32 rows), p_l (32 columns)
-    __shared__ Mirror mirror[4];
+__device__ __forceinline__ void s4_f32_block(const BatchArgs& p, unsigned block, S4F32Lds& lds) {
+    auto& sm = lds.sm;
+    auto& ps = lds.ps;
+    auto& mirror = lds.mirror;
 
     Block bk;
     View v;
-    if (!resolve_block(p, bk, v)) return;
+    if (!resolve_block(p, bk, v, block)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
@@ -664,6 +677,12 @@ __global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
     }
 }
 
+template <bool ONE_BATCH>
+__global__ __launch_bounds__(kS4Threads, 2) void k_s4_mfma_f32(BatchArgs p) {
+    __shared__ S4F32Lds lds;
+    s4_f32_block<ONE_BATCH>(p, blockIdx.x, lds);
+}
+
 // ------------------------------------------------------------------ S4, one channel, matrix cores
 // The same sums as k_s4_mfma_f32, with the frame contractions on the matrix
 // cores (v_mfma_f32_32x32x16_bf16, FP32 accumulation).  Each FP32 operand x is
@@ -760,16 +779,23 @@ __device__ __forceinline__ float stage_rows(uint32_t (*op)[kOpDw], int col, int 
 }
 
 // ONE_BATCH: every chunk fits one frame batch (m <= 10, compile-time).
+struct S4Bf16Lds {
+    __attribute__((aligned(16))) uint32_t opK[3 * kTile][kOpDw];
+    __attribute__((aligned(16))) uint32_t opL[3 * kTile][kOpDw];
+    double psum[2][kTile];          // -gamma p_k (k side), p_l (l side)
+    Mirror mirror[4];
+};
+
 template <bool ONE_BATCH>
-__global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
-    __shared__ __attribute__((aligned(16))) uint32_t opK[3 * kTile][kOpDw];
-    __shared__ __attribute__((aligned(16))) uint32_t opL[3 * kTile][kOpDw];
-    __shared__ double psum[2][kTile];          // -gamma p_k (k side), p_l (l side)
-    __shared__ Mirror mirror[4];
+__device__ __forceinline__ void s4_bf16_block(const BatchArgs& p, unsigned block, S4Bf16Lds& lds) {
+    auto& opK = lds.opK;
+    auto& opL = lds.opL;
+    auto& psum = lds.psum;
+    auto& mirror = lds.mirror;
 
     Block bk;
     View v;
-    if (!resolve_block(p, bk, v)) return;
+    if (!resolve_block(p, bk, v, block)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
@@ -911,6 +937,12 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
         }
     }
     }
+}
+
+template <bool ONE_BATCH>
+__global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_bf16(BatchArgs p) {
+    __shared__ S4Bf16Lds lds;
+    s4_bf16_block<ONE_BATCH>(p, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------ S4, one channel, FP16 x 2 scaled
@@ -1264,13 +1296,18 @@ struct S4Stage {
     double2 pw[2][kTile];               // [side][column]: (p, s^2)
 };
 
-__global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p) {
-    __shared__ __attribute__((aligned(16))) S4Stage stage[kS4Stages];
-    __shared__ Mirror mirror[4];
+struct S4PreLds {
+    __attribute__((aligned(16))) S4Stage stage[kS4Stages];
+    Mirror mirror[4];
+};
+
+__device__ __forceinline__ void s4_pre_block(const BatchArgs& p, unsigned block, S4PreLds& lds) {
+    auto& stage = lds.stage;
+    auto& mirror = lds.mirror;
 
     Block bk;
     View v;
-    if (!resolve_block(p, bk, v)) return;
+    if (!resolve_block(p, bk, v, block)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
@@ -1465,6 +1502,36 @@ __global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p)
         }
     }
     }
+}
+
+__global__ __launch_bounds__(kS4MThreads, 2) void k_s4_mfma_f16_pre(BatchArgs p) {
+    __shared__ S4PreLds lds;
+    s4_pre_block(p, blockIdx.x, lds);
+}
+
+// ------------------------------------------------------------------ S3 and S4, one channel, in one launch
+// Blocks [0, n3) are S3's, the rest S4's: S4 starts as S3 drains, and one launch
+// is saved.  Both kernels take two blocks of 256 threads per CU, so neither gives
+// up anything.  Measured, S3 + S4 one after the other and together: 9.0 + 7.2 and
+// 9.6 us (51200 samples, N_f = 64), 22.6 + 13.2 and 31.9 (2^20, N_f = 200),
+// 205 + 205 and 372 (409 records of one chunk, N_f = 256), 6130 + 3454 and 9382
+// (10^8, N_f = 2048, FP32); 15.86 + 4.77 and 20.70 ms (2^28, N_f = 2048, scaled
+// FP16 x 2).
+template <int KIND>
+__global__ __launch_bounds__(kS3Threads, 2) void k_s3_s4(BatchArgs p3, BatchArgs p4, unsigned n3) {
+    __shared__ union {
+        S3Lds<kFrameBatchSmall> s3;
+        std::conditional_t<KIND == kS4F32, S4F32Lds, std::conditional_t<KIND == kS4Bf16, S4Bf16Lds, S4PreLds>> s4;
+    } lds;
+    static_assert(kS4Threads == kS3Threads && kS4MThreads == kS3Threads, "one block size");
+    if (blockIdx.x < n3) {
+        s3_block<kFrameBatchSmall>(p3, blockIdx.x, lds.s3);
+        return;
+    }
+    const unsigned block = blockIdx.x - n3;
+    if constexpr (KIND == kS4F32) s4_f32_block<true>(p4, block, lds.s4);
+    else if constexpr (KIND == kS4Bf16) s4_bf16_block<true>(p4, block, lds.s4);
+    else s4_pre_block(p4, block, lds.s4);
 }
 
 // ------------------------------------------------------------------ S4, channel combinations
@@ -2012,6 +2079,22 @@ hipError_t launch_s3(const BatchArgs& a, hipStream_t s) {
         case 12: k_s3<12><<<g, kS3Threads, 0, s>>>(a); break;
         case 13: k_s3<13><<<g, kS3Threads, 0, s>>>(a); break;
         default: k_s3<kFrameBatch><<<g, kS3Threads, 0, s>>>(a); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_s3_s4(const BatchArgs& a3, const BatchArgs& a4, S4Kind kind, hipStream_t s) {
+    const dim3 g3 = item_grid(a3), g4 = item_grid(a4);
+    if (g3.x == 0 || g4.x == 0 || a3.m > kFrameBatchSmall || a4.m > kS4FFrames || a4.m > kMfmaFrames)
+        return hipErrorInvalidValue;
+    if ((uint64_t)g3.x + g4.x > 0xffffffu) return hipErrorInvalidConfiguration;
+    const dim3 g(g3.x + g4.x);
+    switch (kind) {
+        case kS4F32: k_s3_s4<kS4F32><<<g, kS3Threads, 0, s>>>(a3, a4, g3.x); break;
+        case kS4Bf16: k_s3_s4<kS4Bf16><<<g, kS3Threads, 0, s>>>(a3, a4, g3.x); break;
+        default:
+            if (!a4.op4) return hipErrorInvalidValue;
+            k_s3_s4<kS4Pre><<<g, kS3Threads, 0, s>>>(a3, a4, g3.x);
     }
     return hipGetLastError();
 }

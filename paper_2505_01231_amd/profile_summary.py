@@ -52,6 +52,7 @@ def s3_source_digest() -> str:
         (src, r"__device__ __forceinline__ bool resolve_block\(.*?\n\}\n"),
         (src, r"__device__ __forceinline__ bool next_item\(.*?\n\}\n"),
         (src, r"template <int FB, bool DIAG>\n__device__ __forceinline__ void s3_item\(.*?\n\}\n"),
+        (src, r"template <int FB>\n__device__ __forceinline__ void s3_block\(.*?\n\}\n"),
         (src, r"template <int FB>\n__global__ __launch_bounds__\(kS3Threads, 2\) void k_s3\(BatchArgs p\) \{.*?\n\}\n"),
         (inc, r"struct Sched \{.*?\n\};\n"),
     ]
