@@ -106,29 +106,55 @@ __device__ __forceinline__ constexpr int opos(int k) {
 }
 
 // Pair of consecutive samples (2n, 2n+1) as float2: one vector load when the
-// frame is aligned for it, two scalar loads otherwise.
+// frame is aligned for it, two scalar loads otherwise.  The pointer comes from a
+// table of records, so the compiler cannot tell that it is device memory: flat
+// loads, an address register pair for each, and of double precision's 16 each
+// waited for the one before.  Measured with device-memory loads, the batches of
+// load_pairs and of the last columns' twiddles: 9.0 -> 6.2 us (51200 samples in
+// double precision, N = 256), 10.6 -> 8.0 (2^20, N = 1024), 21.5 -> 18.5 (2^22),
+// 19.5 -> 15.8 (four windows of 2^20, N = 4096), 265 -> 249 (2^27, N = 1024).
 template <typename T>
-__device__ __forceinline__ float2 sample_pair(const T* __restrict__ xf, int n, bool vec);
-template <>
-__device__ __forceinline__ float2 sample_pair<float>(const float* __restrict__ xf, int n, bool vec) {
-    if (vec) return reinterpret_cast<const float2*>(xf)[n];
-    return make_float2(xf[2 * n], xf[2 * n + 1]);
-}
-template <>
-__device__ __forceinline__ float2 sample_pair<double>(const double* __restrict__ xf, int n, bool vec) {
+__device__ __forceinline__ float2 sample_pair(const T* __restrict__ xf, int n, bool vec) {
+#if defined(__HIP__)
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) T2 GlobalT2;
+    typedef const __attribute__((address_space(1))) T GlobalT;
     if (vec) {
-        const double2 d = reinterpret_cast<const double2*>(xf)[n];
+        const T2 d = ((GlobalT2*)xf)[n];
         return make_float2((float)d.x, (float)d.y);
     }
+    return make_float2((float)((GlobalT*)xf)[2 * n], (float)((GlobalT*)xf)[2 * n + 1]);
+#else
+    (void)vec;
     return make_float2((float)xf[2 * n], (float)xf[2 * n + 1]);
+#endif
 }
-template <>
-__device__ __forceinline__ float2 sample_pair<int16_t>(const int16_t* __restrict__ xf, int n, bool vec) {
-    if (vec) {
-        const short2 d = reinterpret_cast<const short2*>(xf)[n];
-        return make_float2((float)d.x, (float)d.y);
+
+// x is computed by here, and what uses t after it is computed later.
+__device__ __forceinline__ void formed_here(float2& x, int& t) {
+#if defined(__HIP__)
+    asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(t));
+#else
+    (void)x;
+    (void)t;
+#endif
+}
+
+// The 16 pairs t + r Tn.  Double precision's come in two batches, the second
+// (and the window) requested once the first is converted: 16 in flight do not
+// fit the registers.
+template <typename T>
+__device__ __forceinline__ void load_pairs(float2 (&x)[16], const T* __restrict__ xf, int& t, int Tn, bool vec) {
+    constexpr int B = sizeof(T) == 8 ? 8 : 16;
+#pragma unroll
+    for (int r0 = 0; r0 < 16; r0 += B) {
+#pragma unroll
+        for (int r = r0; r < r0 + B; ++r) x[r] = sample_pair(xf, t + r * Tn, vec);
+        if (B < 16) {
+#pragma unroll
+            for (int r = r0; r < r0 + B; ++r) formed_here(x[r], t);
+        }
     }
-    return make_float2((float)xf[2 * n], (float)xf[2 * n + 1]);
 }
 
 template <typename T>
@@ -141,13 +167,8 @@ __device__ __forceinline__ void load_first(float2 (&v)[16], const T* __restrict_
     }
     // One branch per frame (the alignment is the frame's), not one per load.
     float2 x[16];
-    if ((reinterpret_cast<uintptr_t>(xf) % (2 * sizeof(T))) == 0) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = sample_pair(xf, t + r * Tn, true);
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = sample_pair(xf, t + r * Tn, false);
-    }
+    if ((reinterpret_cast<uintptr_t>(xf) % (2 * sizeof(T))) == 0) load_pairs(x, xf, t, Tn, true);
+    else load_pairs(x, xf, t, Tn, false);
     const float2* __restrict__ g2 = reinterpret_cast<const float2*>(g);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -157,21 +178,20 @@ __device__ __forceinline__ void load_first(float2 (&v)[16], const T* __restrict_
 }
 
 // Complex samples (n = t + r Tn) times the real window g_n.
-template <typename T2>
-__device__ __forceinline__ void load_first_cplx(float2 (&v)[16], const T2* __restrict__ xf,
+template <typename T>
+__device__ __forceinline__ void load_first_cplx(float2 (&v)[16], const T* __restrict__ xf,
                                                 const float* __restrict__ g, int t, int Tn, bool live) {
     if (!live) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = make_float2(0.f, 0.f);
         return;
     }
-    T2 x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = xf[t + r * Tn];
+    float2 x[16];
+    load_pairs(x, xf, t, Tn, true);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float w = g[t + r * Tn];
-        v[r] = make_float2(w * (float)x[r].x, w * (float)x[r].y);
+        v[r] = make_float2(w * x[r].x, w * x[r].y);
     }
 }
 
@@ -255,8 +275,8 @@ __device__ __forceinline__ void window_rfft_block(const FftClass& a, int64_t blk
     float2 v[16], w2[16], w3[16];
     if constexpr (R2 > 0) pass_twiddles<LOG2M, R2>(w2, t, 16, tw + N);
     if constexpr (CPLX) {
-        if (rec.dtype == 3) load_first_cplx(v, static_cast<const float2*>(rec.data) + off, g, t, Tn, live);
-        else load_first_cplx(v, static_cast<const double2*>(rec.data) + off, g, t, Tn, live);
+        if (rec.dtype == 3) load_first_cplx(v, static_cast<const float*>(rec.data) + 2 * off, g, t, Tn, live);
+        else load_first_cplx(v, static_cast<const double*>(rec.data) + 2 * off, g, t, Tn, live);
     } else {
         if (rec.dtype == 0) load_first(v, static_cast<const float*>(rec.data) + off, g, t, Tn, live);
         else if (rec.dtype == 1) load_first(v, static_cast<const double*>(rec.data) + off, g, t, Tn, live);
@@ -269,12 +289,10 @@ __device__ __forceinline__ void window_rfft_block(const FftClass& a, int64_t blk
     if constexpr (R3 > 0) fft_pass<LOG2M, R3, false>(v, w3, s, t, 16 * R2);
 
     if (!live) return;
-    // K <= M + 1: at most KMAX outputs per thread, unrolled so that their
-    // twiddle loads are issued together.
-    constexpr int KMAX = (M + 1 + Tn - 1) / Tn;
-    const int K = a.K;
+    const int K = a.K;                            // K <= M + 1
     float2* o = a.out + c * a.out_chan_stride + (gf - a.out_g0) * K;
     if constexpr (CPLX) {
+        constexpr int KMAX = (M + 1 + Tn - 1) / Tn;
 #pragma unroll
         for (int i = 0; i < KMAX; ++i) {
             const int col = t + i * Tn;
@@ -283,19 +301,44 @@ __device__ __forceinline__ void window_rfft_block(const FftClass& a, int64_t blk
         }
         return;
     }
-#pragma unroll
-    for (int i = 0; i < KMAX; ++i) {
-        const int k = t + i * Tn;
-        if (k >= K) break;
+    // Output k = e_k + w_k (X_k - conj X_{M-k}) (-j/2) from X_k and X_{M-k}.  The
+    // roundings are spelled out, since which of two products is fused is the
+    // compiler's choice: of columns t and M the halves er, ei are formed first, of
+    // the others the products with w.
+    auto combine = [&](int k, float2 w, bool halves) {
         const float2 xk = s[pad(k & (M - 1))];
         const float2 xm = s[pad((M - k) & (M - 1))];
-        const float er = 0.5f * (xk.x + xm.x);
-        const float ei = 0.5f * (xk.y - xm.y);
+        const float er = xk.x + xm.x, ei = xk.y - xm.y;
         const float orr = 0.5f * (xk.y + xm.y);   // (X_k - conj X_{M-k}) * (-j/2)
         const float oi = -0.5f * (xk.x - xm.x);
-        const float2 w = tw[k];
-        o[k] = make_float2(er + w.x * orr - w.y * oi, ei + w.x * oi + w.y * orr);
+        const float re = halves ? fmaf(w.x, orr, 0.5f * er) : fmaf(0.5f, er, w.x * orr);
+        const float im = halves ? fmaf(w.x, oi, 0.5f * ei) : fmaf(0.5f, ei, w.x * oi);
+        return make_float2(fmaf(-w.y, oi, re), fmaf(w.y, orr, im));
+    };
+    // Eight columns at a time, their twiddles requested together and all of them
+    // computed before the first is stored (a column after another, each behind
+    // its own bounds check, waited for its twiddle each time).
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (8 * h * Tn >= K) break;
+        float2 w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = t + (8 * h + i) * Tn;
+            w[i] = tw[k < K ? k : K - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = combine(t + (8 * h + i) * Tn, w[i], h + i == 0);
+        int l = t;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) formed_here(w[i], l);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = l + (8 * h + i) * Tn;
+            if (k < K) o[k] = w[i];
+        }
     }
+    if (t + M < K) o[t + M] = combine(t + M, tw[t + M], true);     // column M (t = 0)
 }
 
 template <int LOG2N, bool CPLX>
