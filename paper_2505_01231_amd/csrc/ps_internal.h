@@ -178,7 +178,8 @@ hipError_t launch_power(const CentreArgs& a, hipStream_t s);
 // R = T - T1 remaining tiles hold U = R W units, taken in tile-major order and
 // cut into Q = min(B, U) non-empty runs of equal length (stream-K); run j goes
 // to block j, before its rounds, and touches at most two tiles since R < B.
-// Every piece (one tile, one chunk range) writes its own partial-sum slot:
+// Every piece (one tile, one chunk range) has its own partial-sum slot (a whole
+// tile's stays unwritten where the moment kernel finalizes it, BatchArgs.direct):
 //   whole tile t              -> slot t
 //   run j's piece of tile t   -> slot T1 + j + (t - T1)
 // Runs are ordered and non-empty, so these are distinct and the slots of one
