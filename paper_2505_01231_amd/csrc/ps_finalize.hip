@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256, 8) void k_finalize(FinalizeArgs p) {
         TileLds tile;
         S1Lds s1;
     } sm;
-    int64_t x = blockIdx.x;
+    int64_t x = p.first + blockIdx.x;
     int role = 0;
     while (role < 3 && x >= p.tab[role].n_blocks) x -= p.tab[role++].n_blocks;
     const FinalizeTable& tab = p.tab[role];
@@ -343,7 +343,7 @@ constexpr int64_t kOwnLaunch = 32768;
 
 __global__ __launch_bounds__(256, 8) void k_finalize_tiles(FinalizeArgs p, int role) {
     __shared__ TileLds sm;
-    finalize_tile(p, p.tab[role], blockIdx.x, sm);
+    finalize_tile(p, p.tab[role], p.first + blockIdx.x, sm);
 }
 
 // Running accumulation (ps_stream_*): one block per (segment, tile, group of
@@ -471,16 +471,19 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
     if (!a.s1) b.tab[kFinS1].n_blocks = 0;
     for (int role : {kFinS3, kFinS4}) {
         if (b.tab[role].n_blocks < kOwnLaunch) continue;
-        k_finalize_tiles<<<(unsigned)b.tab[role].n_blocks, 256, 0, s>>>(b, role);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_slices(b.tab[role].n_blocks, [&](int64_t first, unsigned blocks) {
+            b.first = first;
+            k_finalize_tiles<<<blocks, 256, 0, s>>>(b, role);
+        });
         if (e != hipSuccess) return e;
         b.tab[role].n_blocks = 0;
     }
     int64_t n = 0;
     for (const FinalizeTable& t : b.tab) n += t.n_blocks;
-    if (n <= 0) return hipSuccess;
-    k_finalize<<<(unsigned)n, 256, 0, s>>>(b);
-    return hipGetLastError();
+    return launch_slices(n, [&](int64_t first, unsigned blocks) {
+        b.first = first;
+        k_finalize<<<blocks, 256, 0, s>>>(b);
+    });
 }
 
 hipError_t launch_fill_nan(double* p, int64_t n, hipStream_t s) {

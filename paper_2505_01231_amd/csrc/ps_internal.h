@@ -15,6 +15,22 @@
 
 namespace ps {
 
+// Blocks of 256 threads a launch takes.  A dispatch counts its threads in 32
+// bits, and a launch of more is cut down to the count modulo 2^32 with no error
+// (1.7e7 blocks asked for, 222,784 ran).  Larger launches go out in slices.
+constexpr int64_t kMaxBlocks = 0xffffff;
+
+// launch(first, blocks) for consecutive slices of n blocks.
+template <typename Launch>
+hipError_t launch_slices(int64_t n, Launch launch) {
+    for (int64_t first = 0; first < n; first += kMaxBlocks) {
+        launch(first, (unsigned)(n - first < kMaxBlocks ? n - first : kMaxBlocks));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Output-tile edge of the S3 / single-channel S4 kernels: a tile covers 64 x 64
 // (k, l) grid points; the 256 threads of a block each own a 4 x 4 sub-grid.
 constexpr int kTile = 64;
@@ -312,6 +328,7 @@ struct FinalizeArgs {
     int direct;             // tiles of one slot were written by the moment kernels
     const float2* s1;       // per-chunk means of a_0, [C][s1_cs] (S1 only)
     int64_t s1_cs;
+    int64_t first;          // first block of the launch's slice
 };
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
 
