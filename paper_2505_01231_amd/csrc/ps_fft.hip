@@ -24,6 +24,8 @@
 // its frames of M samples are windowed and transformed as they are (the same
 // passes, instantiated for twice the frame length), and column c of the output
 // holds X at bin c - jmax, taken mod M.
+#include <algorithm>
+
 #include "ps_internal.h"
 
 namespace ps {
@@ -740,14 +742,24 @@ __global__ __launch_bounds__(256) void k_window_dft2_few(FftArgs args) {
     }
 }
 
+// One frame length's frames, `frames` a block: launch(args, blocks) per slice.
+template <typename Launch>
+hipError_t launch_frames(const FftArgs& a, int frames, Launch launch) {
+    FftArgs b = a;
+    const int64_t lo = a.cls[0].g_lo, hi = a.cls[0].g_hi;
+    return launch_slices((hi - lo + frames - 1) / frames, [&](int64_t first, unsigned blocks) {
+        b.cls[0].g_lo = lo + first * frames;
+        b.cls[0].g_hi = std::min<int64_t>(hi, b.cls[0].g_lo + (int64_t)blocks * frames);
+        launch(b, blocks);
+    });
+}
+
 hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
     const FftClass& c = a.cls[0];
-    const int64_t n = c.g_hi - c.g_lo;
     if (c.dft_n < 2 || !c.tw64 || c.K < 1) return hipErrorInvalidValue;
     if (c.dft_n1 > 0) {                 // two stages, N = N1 N2
         const int n2 = c.dft_n / c.dft_n1;
         if (n2 * c.dft_n1 != c.dft_n || c.dft_n1 > n2) return hipErrorInvalidValue;
-        if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
         // A quarter of the lanes with rows: 24 rows take 83 us against 156 (2^22
         // samples, N = 1016 = 8 x 127, three frames) and 95 against 154 (N = 3336 =
         // 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against
@@ -756,28 +768,31 @@ hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
         const bool few = F * c.dft_n1 < 16;
         const size_t lds = few ? dft2_few_lds_bytes(c.dft_n, c.dft_n1) : dft2_lds_bytes(c.dft_n, c.dft_n1);
         if (lds > 160 * 1024) return hipErrorInvalidValue;
-        if (few) k_window_dft2_few<<<dim3((unsigned)n, a.n_channels), 256, lds, st>>>(a);
-        else k_window_dft2<<<dim3((unsigned)((n + F - 1) / F), a.n_channels), 256, lds, st>>>(a);
-        return hipGetLastError();
+        return launch_frames(a, few ? 1 : F, [&](const FftArgs& b, unsigned blocks) {
+            const dim3 grid(blocks, b.n_channels);
+            if (few) k_window_dft2_few<<<grid, 256, lds, st>>>(b);
+            else k_window_dft2<<<grid, 256, lds, st>>>(b);
+        });
     }
-    const int64_t bx = (n + kDftFrames - 1) / kDftFrames, bz = (c.K + kDftBins - 1) / kDftBins;
-    if (bx > 0x7fffffff) return hipErrorInvalidConfiguration;
-    k_window_dft<<<dim3((unsigned)bx, a.n_channels, (unsigned)bz), 256, 0, st>>>(a);
-    return hipGetLastError();
+    const unsigned bz = (c.K + kDftBins - 1) / kDftBins;
+    return launch_frames(a, kDftFrames, [&](const FftArgs& b, unsigned blocks) {
+        k_window_dft<<<dim3(blocks, b.n_channels, bz), 256, 0, st>>>(b);
+    });
 }
 
 template <int LOG2N>
 hipError_t launch_n(const FftArgs& a, hipStream_t st) {
     constexpr int M = (1 << LOG2N) / 2, F = kFftThreads / (M / 16);
-    const int64_t n = a.cls[0].g_hi - a.cls[0].g_lo;
-    dim3 grid((unsigned)((n + F - 1) / F), a.n_channels);
-    if (a.cplx) {
-        if constexpr (LOG2N >= 9) k_window_rfft<LOG2N, true><<<grid, kFftThreads, 0, st>>>(a);
-        else return hipErrorInvalidValue;
-    } else {
-        k_window_rfft<LOG2N, false><<<grid, kFftThreads, 0, st>>>(a);
-    }
-    return hipGetLastError();
+    if (a.cplx && LOG2N < 9) return hipErrorInvalidValue;
+    return launch_frames(a, F, [&](const FftArgs& b, unsigned blocks) {
+        const dim3 grid(blocks, b.n_channels);
+        if constexpr (LOG2N >= 9)
+            if (b.cplx) {
+                k_window_rfft<LOG2N, true><<<grid, kFftThreads, 0, st>>>(b);
+                return;
+            }
+        k_window_rfft<LOG2N, false><<<grid, kFftThreads, 0, st>>>(b);
+    });
 }
 
 // a_k(f) -= (1/m) sum_{f' in chunk} a_k(f'), in place, one thread per (chunk, k).
@@ -996,24 +1011,34 @@ int64_t centre_blocks(const CentreArgs& a) {
     return nx;
 }
 
+// Slice arguments of a launch whose classes are block ranges: the slice's
+// block 0 is block `first` of the whole.
+template <typename Args>
+void shift_classes(Args& slice, const Args& whole, int64_t first) {
+    for (int i = 0; i < whole.n_cls; ++i) slice.cls[i].block0 = whole.cls[i].block0 - first;
+}
+
 }  // namespace
 
 hipError_t launch_power(const CentreArgs& a, hipStream_t s) {
     const int64_t nx = centre_blocks(a);
     if (nx == 0) return hipSuccess;
     if (nx < 0 || !power_supported(a.n_channels, a.m)) return hipErrorInvalidValue;
-    if (nx > 0x7fffffff) return hipErrorInvalidConfiguration;
-    const dim3 g((unsigned)nx);
+    void (*kernel)(CentreArgs) = nullptr;
     switch (a.n_channels * 2 + (a.m > 16)) {
-        case 2: k_power<1, 16><<<g, 256, 0, s>>>(a); break;
-        case 3: k_power<1, 32><<<g, 256, 0, s>>>(a); break;
-        case 4: k_power<2, 16><<<g, 256, 0, s>>>(a); break;
-        case 5: k_power<2, 32><<<g, 256, 0, s>>>(a); break;
-        case 6: k_power<3, 16><<<g, 256, 0, s>>>(a); break;
-        case 8: k_power<4, 16><<<g, 256, 0, s>>>(a); break;
+        case 2: kernel = k_power<1, 16>; break;
+        case 3: kernel = k_power<1, 32>; break;
+        case 4: kernel = k_power<2, 16>; break;
+        case 5: kernel = k_power<2, 32>; break;
+        case 6: kernel = k_power<3, 16>; break;
+        case 8: kernel = k_power<4, 16>; break;
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    CentreArgs b = a;
+    return launch_slices(nx, [&](int64_t first, unsigned blocks) {
+        shift_classes(b, a, first);
+        kernel<<<blocks, 256, 0, s>>>(b);
+    });
 }
 
 hipError_t launch_window_rfft(const FftArgs& a, hipStream_t s) {
@@ -1029,10 +1054,11 @@ hipError_t launch_window_rfft(const FftArgs& a, hipStream_t s) {
             if (c.block0 != blocks || c.g_hi < c.g_lo || c.log2n < 8 || c.log2n > 13) return hipErrorInvalidValue;
             blocks += (c.g_hi - c.g_lo + F - 1) / F;
         }
-        if (blocks <= 0) return hipSuccess;
-        if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-        k_window_rfft_multi<<<dim3((unsigned)blocks, a.n_channels), kFftThreads, 0, s>>>(a);
-        return hipGetLastError();
+        FftArgs b = a;
+        return launch_slices(blocks, [&](int64_t first, unsigned n) {
+            shift_classes(b, a, first);
+            k_window_rfft_multi<<<dim3(n, a.n_channels), kFftThreads, 0, s>>>(b);
+        });
     }
     const FftClass& c0 = a.cls[0];
     if (c0.g_hi <= c0.g_lo || c0.n_recs <= 0) return hipSuccess;
@@ -1055,10 +1081,11 @@ hipError_t launch_centre(const CentreArgs& a, hipStream_t s) {
     const int64_t nx = centre_blocks(a);
     if (nx == 0) return hipSuccess;
     if (nx < 0) return hipErrorInvalidValue;
-    if (nx > 0x7fffffff) return hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)nx, a.n_channels);
-    k_centre<<<grid, 256, 0, s>>>(a);
-    return hipGetLastError();
+    CentreArgs b = a;
+    return launch_slices(nx, [&](int64_t first, unsigned blocks) {
+        shift_classes(b, a, first);
+        k_centre<<<dim3(blocks, a.n_channels), 256, 0, s>>>(b);
+    });
 }
 
 }  // namespace ps

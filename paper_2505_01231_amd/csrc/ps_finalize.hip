@@ -440,6 +440,7 @@ __global__ void k_zscore(const double* a, const double* ae, const double* b, con
 
 hipError_t launch_accumulate(const AccumArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (a.n_items > kMaxBlocks) return hipErrorInvalidConfiguration;
     k_accumulate<<<(unsigned)a.n_items, 256, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -461,8 +462,10 @@ hipError_t launch_finalize_s1_sums(const double* state, int n_channels, int64_t 
 hipError_t launch_zscore(const double* a, const double* ae, const double* b, const double* be, int64_t n,
                          double* out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    k_zscore<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, ae, b, be, n, out);
-    return hipGetLastError();
+    return launch_slices((n + 255) / 256, [&](int64_t first, unsigned blocks) {
+        const int64_t i = 256 * first;
+        k_zscore<<<blocks, 256, 0, s>>>(a + i, ae + i, b + i, be + i, n - i, out + i);
+    });
 }
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
@@ -488,8 +491,9 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
 
 hipError_t launch_fill_nan(double* p, int64_t n, hipStream_t s) {
     if (!p || n <= 0) return hipSuccess;
-    k_fill_nan<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n);
-    return hipGetLastError();
+    return launch_slices((n + 255) / 256, [&](int64_t first, unsigned blocks) {
+        k_fill_nan<<<blocks, 256, 0, s>>>(p + 256 * first, n - 256 * first);
+    });
 }
 
 }  // namespace ps

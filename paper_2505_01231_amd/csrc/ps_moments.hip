@@ -2052,9 +2052,11 @@ int blocks_per_cu(const void* fn, int threads) {
 }  // namespace
 
 static dim3 item_grid(const BatchArgs& a) { return dim3((unsigned)(((a.n_items + 7) / 8) * 8)); }
+static bool too_many(const BatchArgs& a) { return a.n_items > kMaxBlocks - 7; }
 
 hipError_t launch_s2(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     k_s2<<<item_grid(a), 256, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -2069,6 +2071,7 @@ bool s3_small_batch(int m) { return m <= kFrameBatchSmall || m % kFrameBatchSmal
 
 hipError_t launch_s3(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     const int fb = a.s3_fb ? a.s3_fb
                    : (!s3_small_batch(a.m) && a.m <= 13) ? a.m
                                                         : kFrameBatchSmall;
@@ -2101,6 +2104,7 @@ hipError_t launch_s3_s4(const BatchArgs& a3, const BatchArgs& a4, S4Kind kind, h
 
 hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     if (a.m <= kS4FFrames)
         k_s4_mfma_f32<true><<<item_grid(a), kS4Threads, 0, s>>>(a);
     else
@@ -2110,6 +2114,7 @@ hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s) {
 
 hipError_t launch_s4_mfma(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     if (a.m <= kMfmaFrames)
         k_s4_mfma_bf16<true><<<item_grid(a), kS4MThreads, 0, s>>>(a);
     else
@@ -2119,6 +2124,7 @@ hipError_t launch_s4_mfma(const BatchArgs& a, hipStream_t s) {
 
 hipError_t launch_s4_cross_mfma(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     if (a.m <= kMfmaFrames)
         k_s4_cross_mfma<true><<<item_grid(a), kS4XMThreads, 0, s>>>(a);
     else
@@ -2132,6 +2138,7 @@ int s4_cross_mfma_blocks_per_cu() {
 
 hipError_t launch_s4_cross(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     k_s4_cross_f32<<<item_grid(a), kS4XThreads, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -2148,6 +2155,7 @@ int s4_blocks_per_cu() {
 }
 hipError_t launch_s4_mfma_f16(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
+    if (too_many(a)) return hipErrorInvalidConfiguration;
     if (a.op4) {
         if (a.m > kOpFrames) return hipErrorInvalidValue;
         k_s4_mfma_f16_pre<<<item_grid(a), kS4MThreads, 0, s>>>(a);

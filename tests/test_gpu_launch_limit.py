@@ -23,3 +23,25 @@ def test_sequential_of_a_million_chunks(n_chunks):
                 assert torch.isfinite(b).all() and (b != 0).any(), (k, lo)
                 assert torch.equal(a, b), (k, lo)
         torch.cuda.synchronize()
+
+
+# A chunk repeated 2^24 + 4096 times: one block each in the centring pass (and in
+# k_power, S1 and S2 alone).  Every chunk's estimate is the same: n equal FP64
+# terms in any order are off by n 2^-53 = 2e-9 at most, and the variance of the
+# mean by as much of the mean squared, over n: sigma below 2e-8 of the mean.
+@pytest.mark.parametrize("orders,m", [((1, 2), 2), ((1, 2, 3), 3)])
+def test_record_of_more_chunks_than_a_launch_has_blocks(orders, m):
+    from paper_2505_01231_amd import Plan
+    n = (1 << 24) + 4096
+    print("[gpu-case] record of", n, "chunks", orders, flush=True)
+    g = torch.Generator().manual_seed(m)
+    c = (torch.randn(256 * m, generator=g) * 1000 + 50).to(torch.int16).to("cuda:0")
+    with Plan(frame_len=256, n_freq=1, m=m, orders=orders) as p:
+        one, many = p.execute(c), p.execute(c.repeat(n))
+        torch.cuda.synchronize()
+        assert many.n_chunks == n
+        for o in orders:
+            a, b, e = getattr(one, f"s{o}"), getattr(many, f"s{o}"), getattr(many, f"s{o}_err")
+            assert torch.isfinite(a).all() and a.abs().max() > 0, o
+            assert (a - b).abs().max() <= 1e-8 * a.abs().max(), o
+            assert e.abs().max() <= 1e-7 * a.abs().max(), o
