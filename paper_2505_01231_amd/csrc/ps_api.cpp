@@ -1421,7 +1421,7 @@ ps_status launch_moments(ps_plan_t p, const Batch& B, const Group& G, char* ws, 
     };
     // S3 and the single-channel S4 in one launch (stage timing keeps them apart)
     const bool s4_merges = p->precision != PS_PREC_FP16X2S || p->s4_pre;
-    if (G.s3.n_items && G.s4s.n_items && !p->prof && !p->c3opt() && p->m <= ps::kFrameBatchSmall &&
+    if (ps::s3_s4_supported(G.s3.n_items, G.s4s.n_items, p->m) && !p->prof && !p->c3opt() &&
         (p->s3_fb == 0 || p->s3_fb == ps::kFrameBatchSmall) && s4_merges) {
         const ps::S4Kind kind = p->precision == PS_PREC_FP32     ? ps::kS4F32
                                 : p->precision == PS_PREC_BF16X3 ? ps::kS4Bf16

@@ -292,8 +292,14 @@ struct BatchArgs {
 constexpr int kPairFrames = 10;
 hipError_t launch_s2(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s3(const BatchArgs& a, hipStream_t s);
-// S3 and the single-channel S4 in one launch: up to 10 rows per chunk in both.
+// Blocks of a moment launch: the items in whole rounds over the eight XCDs.
+inline int64_t item_blocks(int64_t n_items) { return (n_items + 7) / 8 * 8; }
+// S3 and the single-channel S4 in one launch: up to 10 rows per chunk in both,
+// and no more blocks than a launch takes (two launches take as many each).
 enum S4Kind { kS4F32, kS4Bf16, kS4Pre };
+inline bool s3_s4_supported(int64_t items3, int64_t items4, int rows) {
+    return items3 > 0 && items4 > 0 && rows <= kFrameBatchSmall && item_blocks(items3) + item_blocks(items4) <= kMaxBlocks;
+}
 hipError_t launch_s3_s4(const BatchArgs& s3, const BatchArgs& s4, S4Kind kind, hipStream_t s);
 hipError_t launch_s4_single(const BatchArgs& a, hipStream_t s);
 hipError_t launch_s4_mfma(const BatchArgs& a, hipStream_t s);

@@ -26,6 +26,7 @@
 // by the hardware; the ids are remapped so that each XCD sees a contiguous
 // range of blocks: the tiles of one round on one XCD then walk the same chunks
 // at the same time and share their coefficients in that XCD's L2.
+#include <algorithm>
 #include <type_traits>
 
 #include "ps_internal.h"
@@ -2051,8 +2052,8 @@ int blocks_per_cu(const void* fn, int threads) {
 
 }  // namespace
 
-static dim3 item_grid(const BatchArgs& a) { return dim3((unsigned)(((a.n_items + 7) / 8) * 8)); }
-static bool too_many(const BatchArgs& a) { return a.n_items > kMaxBlocks - 7; }
+static dim3 item_grid(const BatchArgs& a) { return dim3((unsigned)item_blocks(a.n_items)); }
+static bool too_many(const BatchArgs& a) { return item_blocks(a.n_items) > kMaxBlocks; }
 
 hipError_t launch_s2(const BatchArgs& a, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
@@ -2087,11 +2088,9 @@ hipError_t launch_s3(const BatchArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_s3_s4(const BatchArgs& a3, const BatchArgs& a4, S4Kind kind, hipStream_t s) {
-    const dim3 g3 = item_grid(a3), g4 = item_grid(a4);
-    if (g3.x == 0 || g4.x == 0 || a3.m > kFrameBatchSmall || a4.m > kS4FFrames || a4.m > kMfmaFrames)
-        return hipErrorInvalidValue;
-    if ((uint64_t)g3.x + g4.x > 0xffffffu) return hipErrorInvalidConfiguration;
-    const dim3 g(g3.x + g4.x);
+    static_assert(kFrameBatchSmall <= kS4FFrames && kFrameBatchSmall <= kMfmaFrames, "one batch in both");
+    if (!s3_s4_supported(a3.n_items, a4.n_items, std::max(a3.m, a4.m))) return hipErrorInvalidValue;
+    const dim3 g3 = item_grid(a3), g(g3.x + item_grid(a4).x);
     switch (kind) {
         case kS4F32: k_s3_s4<kS4F32><<<g, kS3Threads, 0, s>>>(a3, a4, g3.x); break;
         case kS4Bf16: k_s3_s4<kS4Bf16><<<g, kS3Threads, 0, s>>>(a3, a4, g3.x); break;

@@ -1,6 +1,7 @@
 // Host driver of the launchers' slicing (test infrastructure only): launch_slices,
-// launch_frames and shift_classes of the library's sources with counts around
-// and above the blocks one launch takes.  Prints the first fault and fails.
+// launch_frames, shift_classes and the rule for S3 and S4 in one launch, from the
+// library's sources, with counts around and above the blocks one launch takes.
+// Prints the first fault and fails.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -64,5 +65,14 @@ int main() {
             check(cs == cw && x - s.cls[cs].block0 == x + first - w.cls[cw].block0, "class of a block", x + first);
         }
     }
+    // S3 and S4 share a launch while their blocks together fit one
+    check(ps::s3_s4_supported(1, 1, 10) && !ps::s3_s4_supported(1, 1, 11), "rows", 1);
+    check(!ps::s3_s4_supported(0, 5, 10) && !ps::s3_s4_supported(5, 0, 10), "nothing to merge", 0);
+    const int64_t half = (L + 1) / 2 - 8;       // a multiple of 8
+    check(ps::s3_s4_supported(half, half, 10), "two halves", half);
+    check(ps::s3_s4_supported(half, half + 8, 10), "all blocks", half);
+    check(!ps::s3_s4_supported(half, half + 9, 10), "one round too many", half);
+    check(!ps::s3_s4_supported(half + 8, half + 8, 10), "more than a launch", half);
+    check(!ps::s3_s4_supported(L - 7, L - 7, 10), "as many as separate launches take", L);
     return 0;
 }

@@ -1,6 +1,7 @@
 """The launchers' slicing (a dispatch counts its threads in 32 bits), compiled
-from the library's own sources for the CPU: every block and frame of a launch
-goes out once, whatever the count (test infrastructure; no GPU)."""
+from the library's own sources for the CPU: every block and frame of a launch goes
+out once, whatever the count, and S3 and S4 share a launch only while both fit
+(test infrastructure; no GPU)."""
 import os
 import re
 import shutil
