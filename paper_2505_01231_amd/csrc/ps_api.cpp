@@ -635,6 +635,14 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 const int64_t tiles = !direct_tiles ? sg.n_tiles : sg.n_chunks == 1 ? 0 : sc.R();
                 return tiles * (points / 256);
             };
+            // Its partial-sum slots, laid out next.  A record of one chunk whose tiles
+            // the moment kernels finalize has none (409 such records, N_f = 256: 0.8 GB).
+            auto grid_slots = [&](const ps::Seg& sg, int64_t points) {
+                const int64_t at = part;
+                if (!direct_tiles || sg.n_chunks > 1)
+                    part += ps::Sched{sg.n_tiles, sg.n_chunks, sg.blocks}.n_slots() * sg.ncomp * points;
+                return at;
+            };
             ps::Seg base{};
             // the record's chunk 0 (per-chunk schedule: the class block holds the current chunk)
             base.coef = (int64_t)(k.coef_off / sizeof(float2)) + (per_chunk ? 0 : q.frame0 * K);
@@ -692,13 +700,12 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                     sg.coef = (int64_t)(k.coef3_off / sizeof(float2)) + (per_chunk ? 0 : q.chunk0c * (m + 1) * K);
                     sg.cs = k.rows3 * K;
                 }
-                sg.part = part;
-                part += ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * 4 * TT;
+                sg.ncomp = 4;
+                sg.part = grid_slots(sg, TT);
                 sg.out = o && o->d_s3 ? o->d_s3 + 2 * i * nf2 : nullptr;
                 sg.err = o && o->d_s3_err ? o->d_s3_err + 2 * i * nf2 : nullptr;
                 sg.scale = scl.s3;
                 sg.sym = sym;
-                sg.ncomp = 4;
                 G.s3.add(sg, sg.blocks);
                 if (grid_items(sg, TT) || !direct_tiles) finalize(G.f3, fin3, i, sg, grid_items(sg, TT));
             }
@@ -723,14 +730,9 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                     sg.p4_cs = k.op_chunks * 2 * ngp;
                 }
                 // (a pair's two combinations have the same tiles and blocks)
-                const int64_t n_part = ps::Sched{sg.n_tiles, q.Np, sg.blocks}.n_slots() * sg.ncomp * (single ? TT : TX);
                 if (first) {
-                    sg.part = part4[i] = part;
-                    part += n_part;
-                    if (pair >= 0) {
-                        part4[pair] = part;
-                        part += n_part;
-                    }
+                    sg.part = part4[i] = grid_slots(sg, single ? TT : TX);
+                    if (pair >= 0) part4[pair] = grid_slots(sg, TX);
                 } else {
                     sg.part = part4[i];
                 }
@@ -741,6 +743,7 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 if (first) {
                     ps::Seg ms = sg;
                     if (pair >= 0) {
+                        ms.n_chunks2 = 1;
                         ms.part2 = part4[pair];
                         ms.p4 = (int64_t)(uintptr_t)(o && o->d_s4 ? o->d_s4 + 2 * pair * nf2 : nullptr);
                         ms.p4_cs = (int64_t)(uintptr_t)(o && o->d_s4_err ? o->d_s4_err + 2 * pair * nf2 : nullptr);

@@ -232,7 +232,7 @@ struct Seg {
     // start), op4_cs = 1: the segment takes those in place of coefficients.
     int64_t op4, op4_cs;
     // and its (column sum of P, scale s^2) pairs (double offset), channel stride.
-    // Cross-channel S4 stage with part2: the addresses of the second
+    // Cross-channel S4 stage with n_chunks2: the addresses of the second
     // combination's spectrum and error bar.
     // S2 finalize with blocks == 0 (no partial sums: the chunk terms themselves
     // are added): p4 the shifted frame set's chunk terms.
@@ -253,8 +253,8 @@ struct Seg {
     int32_t ncomp;          // finalize: 4 (complex) or 2 (real)
     // finalize with interlaced windows: the partial sums of the shifted frame
     // set (its own Sched{n_tiles, n_chunks2, blocks2}); n_chunks2 == 0: none.
-    // Cross-channel S4 stage: the partial sums of the combination (a, b, d, c)
-    // that the segment forms as well (0: none).
+    // Cross-channel S4 stage, n_chunks2 == 1: the segment forms the combination
+    // (a, b, d, c) as well, with its partial sums at part2.
     int64_t part2;
     int32_t n_chunks2;
     int32_t blocks2;

@@ -2033,10 +2033,11 @@ __global__ __launch_bounds__(kS4XMThreads, 2) void k_s4_cross_mfma(BatchArgs p) 
     }
     // (a plane's factors sit at different columns)
     const bool ab = p.s4_shift == 0 && bk.s->ch[0] == bk.s->ch[1], cd = p.s4_shift == 0 && bk.s->ch[2] == bk.s->ch[3];
-    const int64_t pair = bk.s->part2 ? bk.s->part2 - bk.s->part : 0;
+    const bool paired = bk.s->n_chunks2 != 0;
+    const int64_t pair = bk.s->part2 - bk.s->part;
     Item it;
     while (next_item<kTileX, 4>(p, bk, it)) {
-        if (ONE_BATCH && pair) s4_cross_item<ONE_BATCH ? kXPair : kXGeneral, ONE_BATCH>(p, v, *bk.s, it, it.part + pair, sm);
+        if (ONE_BATCH && paired) s4_cross_item<ONE_BATCH ? kXPair : kXGeneral, ONE_BATCH>(p, v, *bk.s, it, it.part + pair, sm);
         else if (ab && cd) s4_cross_item<kXSameBoth, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
         else if (ab) s4_cross_item<kXSameAB, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
         else if (cd) s4_cross_item<kXSameCD, ONE_BATCH>(p, v, *bk.s, it, nullptr, sm);
