@@ -277,7 +277,9 @@ ps_status ps_workspace_size(ps_plan_t plan, const ps_record* recs, int32_t n_rec
  * chunk average with the error bars of Section 4.2.  recs[i] is read-only;
  * outs[i] (caller-owned, layouts of ps_output) receives record i; a record
  * without a complete chunk gets NaN outputs.  d_ws must be 256-byte aligned
- * and at least ps_workspace_size() bytes; its contents are scratch.
+ * and at least ps_workspace_size() bytes; its contents are scratch.  (Up to
+ * 8 GiB of that are S2's chunk terms, which save a pass over the coefficients; a
+ * workspace that lacks no more than those is taken, and does without.)
  * Errors (nothing enqueued): PS_E_INVALID_ARG for NULL, misaligned or
  * inconsistent arguments, PS_E_UNSUPPORTED for a record of more than 2^31 - 1
  * chunks, PS_E_WORKSPACE for a small workspace, PS_E_HIP when a launch fails. */

@@ -454,15 +454,29 @@ Scales spectrum_scales(const ps_plan_s* p, const double* sum_g) {
 
 void finish_layout(const ps_plan_s* p, Batch& B);
 
-// Which S2 pairs the centring pass forms.
+// More bytes of chunk terms than this are not laid out, and S2 comes from the
+// centred coefficients: the terms save a pass over the coefficients (16000 frames
+// of four channels, m = 2: 499 us against 568) but take up to twice their bytes
+// (2^33 samples a channel, m = 2: 155 GB of workspace against 69), and records
+// that filled the card without them have to fit still.
+constexpr size_t kS2TermsBytes = size_t(8) << 30;
+
+// Which S2 pairs the centring pass forms (the batch's classes have their chunks).
 void choose_s2_terms(const ps_plan_s* p, Batch& B) {
-    std::memset(B.s2_entry, -1, sizeof B.s2_entry);
-    B.power = !p->has(3) && !p->has(4) && p->has(2) && ps::power_supported(p->C, p->m);
-    if (!p->has(2) || (!B.power && p->m > ps::kCentreRegs)) return;
+    if (!p->has(2)) return;
+    const bool power = !p->has(3) && !p->has(4) && ps::power_supported(p->C, p->m);
+    if (!power && p->m > ps::kCentreRegs) return;
     for (int i = 0; i < p->n2(); ++i) {
         const int a = p->c2[2 * i], b = p->c2[2 * i + 1];
-        if ((B.power || a == b) && B.s2_entry[a][b] < 0) B.s2_entry[a][b] = (int8_t)B.n_s2_entries++;
+        if ((power || a == b) && B.s2_entry[a][b] < 0) B.s2_entry[a][b] = (int8_t)B.n_s2_entries++;
     }
+    size_t bytes = 0;
+    for (const BatchClass& k : B.bc)
+        bytes += (size_t)B.n_s2_entries * (p->schedule == PS_SCHED_PER_CHUNK ? 1 : k.chunks) * p->fc[k.cls].Ng * sizeof(float2);
+    B.power = power && bytes <= kS2TermsBytes;
+    if (bytes <= kS2TermsBytes) return;
+    std::memset(B.s2_entry, -1, sizeof B.s2_entry);
+    B.n_s2_entries = 0;
 }
 
 // Up to this many chunks the finalize adds S2's chunk terms itself, beside the
@@ -482,7 +496,6 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
     const int n_int = n * B.stride;
     B.ri.assign(n_int, RecInfo{});
     std::memset(B.s2_entry, -1, sizeof B.s2_entry);
-    if (!lean) choose_s2_terms(p, B);
     // chunk counts and frame lengths
     std::vector<int> bc_of(p->fc.size(), -1);
     for (int ir = 0; ir < n_int; ++ir) {
@@ -531,6 +544,7 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
         B.chunks_tot += k.chunks;
     }
     for (RecInfo& q : B.ri) q.chunk0 = B.bc[q.bc].chunk_base + q.chunk0c;
+    if (!lean) choose_s2_terms(p, B);
     // coefficient blocks (the per-chunk schedule holds one chunk per class)
     size_t off = 0;
     for (BatchClass& k : B.bc) {
@@ -757,6 +771,18 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
     }
     B.part_doubles = part;
     finish_layout(p, B);
+}
+
+// The batch laid out for a workspace of `bytes`, without S2's chunk terms where
+// only that fits (a caller's fixed arena then holds as many records as if there
+// were none).  Whether it fits.
+bool build_fitting(const ps_plan_s* p, const ps_record* recs, int n, const ps_output* outs, size_t bytes, Batch& B) {
+    build_batch(p, recs, n, outs, B);
+    if (B.total > bytes && B.n_s2_entries > 0) {
+        B = Batch{};
+        build_batch(p, recs, n, outs, B, /*slots=*/false, /*lean=*/true);
+    }
+    return B.total <= bytes;
 }
 
 // Table region and workspace offsets of a built batch (again after tables
@@ -1676,8 +1702,8 @@ ps_status ps_execute(ps_plan_t p, const ps_record* recs, int32_t n_rec, void* d_
     if (s != PS_OK || n_rec == 0) return s;
     hipStream_t st = (hipStream_t)stream;
     Batch B;
-    build_batch(p, recs, n_rec, outs, B);
-    if (!d_ws || ws_bytes < B.total) return fail(PS_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, B.total);
+    if (!build_fitting(p, recs, n_rec, outs, ws_bytes, B) || !d_ws)
+        return fail(PS_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, B.total);
     char* ws = static_cast<char*>(d_ws);
     if (B.chunks_tot > 0) {
         s = upload_tables(p, B, ws + B.off_tab, st);
@@ -1694,12 +1720,7 @@ ps_status ps_execute_static(ps_plan_t p, const ps_record* recs, int32_t n_rec, c
     if (s != PS_OK || n_rec == 0) return s;
     hipStream_t st = (hipStream_t)stream;
     Batch B;
-    build_batch(p, recs, n_rec, outs, B);
-    if (B.total > ps::kStaticScratchBytes) {
-        B = Batch{};
-        build_batch(p, recs, n_rec, outs, B, /*slots=*/false, /*lean=*/true);
-    }
-    if (B.total > ps::kStaticScratchBytes)
+    if (!build_fitting(p, recs, n_rec, outs, ps::kStaticScratchBytes, B))
         return fail(PS_E_WORKSPACE, "these records need %zu bytes of workspace; the static scratch holds %zu",
                     B.total, ps::kStaticScratchBytes);
     if (B.chunks_tot > 0) {
@@ -1856,8 +1877,8 @@ ps_status ps_graph_create(ps_plan_t p, const ps_record* recs, int32_t n_rec, voi
     ps_status s = validate_execute(p, recs, n_rec, d_ws, outs);
     if (s != PS_OK) return s;
     Batch B;
-    build_batch(p, recs, n_rec, outs, B);
-    if (!d_ws || ws_bytes < B.total) return fail(PS_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, B.total);
+    if (!build_fitting(p, recs, n_rec, outs, ws_bytes, B) || !d_ws)
+        return fail(PS_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, B.total);
     auto* g = new ps_graph_s();
     // Work tables: built once on the host, copied synchronously into device
     // memory that the graph owns (nothing is staged at replay time).

@@ -1,5 +1,12 @@
-"""The workspace holds no partial-sum slots for records of one chunk, which the
-moment kernels finalize."""
+"""What the workspace holds: no partial-sum slots for records of one chunk, which
+the moment kernels finalize, and S2's chunk terms only where they are bounded and
+fit.
+
+Without the terms S2's sums come from the same FP32 chunk terms, formed from the
+coefficients, in another FP64 order: 1e-12 of the largest value, as in the tests
+of the terms."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -57,3 +64,73 @@ def test_one_chunk_without_slots(precision, C, Nf):
                     assert (a - r).abs().max() <= 4 * 2.0 ** -53 * r.abs().max(), (k, i)
                 e, f = getattr(ref[i], k + "_err"), getattr(many[i], k + "_err")
                 assert torch.isnan(e[..., 0]).all() and torch.equal(torch.isnan(e), torch.isnan(f)), (k, i)
+
+
+def _workspace_size(p, n_samples, C_):
+    """ps_workspace_size of a record that is not there (nothing reads it)."""
+    from paper_2505_01231_amd import _lib as L
+    r = L.ps_record()
+    r.d_data, r.n_samples, r.channel_stride, r.dtype = 1 << 20, n_samples, n_samples, L.PS_F32
+    n = C.c_size_t()
+    L.check(p._lib.ps_workspace_size(p._handle, C.byref(r), 1, C.byref(n)), "ps_workspace_size")
+    return n.value
+
+
+# Pairs of four channels at two frames a chunk: more bytes of terms than of
+# coefficients.  Beyond their 8 GiB the workspace is the coefficients', S1's and
+# the slots'.
+@pytest.mark.parametrize("log2n", [20, 28, 33])
+def test_chunk_terms_are_bounded(log2n):
+    from paper_2505_01231_amd import Plan
+    print("[gpu-case] bounded chunk terms", log2n, flush=True)
+    N, m, n = 1024, 2, 1 << log2n
+    with Plan(frame_len=N, n_freq=257, m=m, n_channels=4, orders=(1, 2)) as p:
+        n_chunks = n // (N * m)
+        coefficients, s1, slots = 4 * n_chunks * m * p.n_coef * 8, 4 * n_chunks * 8, 64 << 20
+        assert _workspace_size(p, n, 4) <= coefficients + s1 + slots + (8 << 30)
+        if log2n == 33:
+            assert _workspace_size(p, n, 4) <= coefficients + s1 + slots
+
+
+def _equal(a, b, tol=1e-12):
+    for k in ("s1", "s1_err", "s2", "s2_err", "s3", "s3_err"):
+        x, y = getattr(a, k), getattr(b, k)
+        if x is None:
+            continue
+        assert torch.isfinite(y).all(), k
+        assert (x - y).abs().max() <= tol * y.abs().max(), k
+
+
+# A workspace that lacks half of the chunk terms: the call runs without them, as
+# a graph too; one that lacks the coefficients is refused.
+@pytest.mark.parametrize("orders,C_,m,n_chunks", [((1, 2), 4, 2, 2048), ((1, 2), 1, 20, 700), ((1, 2, 3), 2, 4, 1024)])
+def test_workspace_without_room_for_the_terms(orders, C_, m, n_chunks):
+    from paper_2505_01231_amd import Plan
+    from paper_2505_01231_amd import _lib as L
+    print("[gpu-case] no room for the terms", orders, C_, m, n_chunks, flush=True)
+    N = 512
+    x = _record(N, m, n_chunks, C_, 7)
+    with Plan(frame_len=N, n_freq=65, m=m, n_channels=C_, orders=orders) as p:
+        want = p.execute(x)
+        full = p.workspace_bytes([x])
+        pairs = len(p.combos2) if 3 not in orders else C_
+        terms = pairs * n_chunks * 65 * 8
+        coefficients = C_ * n_chunks * m * p.n_coef * 8
+        ws = torch.full((full - terms // 2,), 0xFF, dtype=torch.uint8, device="cuda:0")
+        st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        rec = (L.ps_record * 1)(p.record(x))
+        out = p.allocate_outputs(x.device)
+        o = (L.ps_output * 1)(out.c_struct())
+        L.check(p._lib.ps_execute(p._handle, rec, 1, ws.data_ptr(), ws.numel(), o, st), "ps_execute")
+        torch.cuda.synchronize()
+        _equal(out, want)
+        g, out = C.c_void_p(), p.allocate_outputs(x.device)
+        o = (L.ps_output * 1)(out.c_struct())
+        L.check(p._lib.ps_graph_create(p._handle, rec, 1, ws.data_ptr(), ws.numel(), o, C.byref(g)), "ps_graph_create")
+        for _ in range(3):
+            ws.fill_(0xFF)
+            L.check(p._lib.ps_graph_launch(g, st), "ps_graph_launch")
+            torch.cuda.synchronize()
+            _equal(out, want)
+        p._lib.ps_graph_destroy(g)
+        assert p._lib.ps_execute(p._handle, rec, 1, ws.data_ptr(), coefficients, o, st) == L.PS_E_WORKSPACE
