@@ -134,3 +134,35 @@ def test_workspace_without_room_for_the_terms(orders, C_, m, n_chunks):
             _equal(out, want)
         p._lib.ps_graph_destroy(g)
         assert p._lib.ps_execute(p._handle, rec, 1, ws.data_ptr(), coefficients, o, st) == L.PS_E_WORKSPACE
+
+
+# The static scratch (256 MiB) holds a record's layout without the terms but not
+# with them: S1 and S2 alone (centred coefficients written instead of held), and
+# S2 beside S3.  The first length above the scratch is searched for, so that the
+# branch is the one taken.
+@pytest.mark.parametrize("orders,C_,m", [((1, 2), 4, 2), ((1, 2), 1, 4), ((1, 2, 3), 1, 4), ((2, 4), 1, 4)])
+def test_static_scratch_without_the_terms(orders, C_, m):
+    from paper_2505_01231_amd import Plan
+    from paper_2505_01231_amd import _lib as L
+    print("[gpu-case] static scratch without the terms", orders, C_, m, flush=True)
+    N, Nf = 512, 65
+    with Plan(frame_len=N, n_freq=Nf, m=m, n_channels=C_, orders=orders) as p:
+        per_chunk = N * m
+        lo, hi = 1, 1 << 21                       # chunks: fits, does not
+        assert _workspace_size(p, hi * per_chunk, C_) > L.PS_STATIC_SCRATCH_BYTES
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if _workspace_size(p, mid * per_chunk, C_) <= L.PS_STATIC_SCRATCH_BYTES else (lo, mid)
+        g = torch.Generator(device="cuda:0").manual_seed(m)
+        x = torch.randn((C_, hi * per_chunk), generator=g, device="cuda:0") + 0.3
+        x = x[0] if C_ == 1 else x
+        assert p.workspace_bytes([x]) > L.PS_STATIC_SCRATCH_BYTES
+        want, out = p.execute(x), p.allocate_outputs(x.device)
+        rec, o = p.record(x), out.c_struct()
+        st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        for _ in range(2):
+            L.check(p._lib.ps_execute_static(p._handle, C.byref(rec), 1, C.byref(o), st), "ps_execute_static")
+            torch.cuda.synchronize()
+            _equal(out, want)
+        if 4 in orders:
+            assert torch.equal(out.s4, want.s4) and torch.equal(out.s4_err, want.s4_err)
