@@ -667,7 +667,7 @@ __global__ __launch_bounds__(256) void k_window_dft2(FftArgs args) {
 
 // The two stages with a product per term and outputs spread over all threads,
 // whatever N1: for lengths with a small N1 and a large N2 (8 x 1021), whose
-// block holds too few rows for the lanes of k_window_dft2.
+// block holds too few rows for the lanes of k_window_dft2 (dft2_takes_few).
 // LDS (dynamic): the N samples (FP32), the exponentials of the two stages
 // exp(+2 pi j t / N1), t < N1, and exp(+2 pi j t / N2), t < N2 (FP64), then Y.
 __host__ __device__ constexpr size_t dft2_few_sx_bytes(int N) { return ((size_t)N * 4 + 15) / 16 * 16; }
@@ -754,29 +754,37 @@ hipError_t launch_frames(const FftArgs& a, int frames, Launch launch) {
     });
 }
 
-hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
+// Whether a two-stage length takes k_window_dft2_few.  With a quarter of the lanes
+// with rows or more k_window_dft2 is the faster: 24 rows take 83 us against 156 (2^22
+// samples, N = 1016 = 8 x 127, three frames) and 95 against 154 (N = 3336 =
+// 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against 303
+// (N = 4072 = 8 x 509).
+bool dft2_takes_few(int N, int N1) { return dft2_frames(N, N1) * N1 < 16; }
+
+// The direct transform's launches: launch(kernel, grid, bytes of LDS, arguments).
+template <typename Launch>
+hipError_t dft_launches(const FftArgs& a, Launch launch) {
     const FftClass& c = a.cls[0];
-    if (c.dft_n < 2 || !c.tw64 || c.K < 1) return hipErrorInvalidValue;
-    if (c.dft_n1 > 0) {                 // two stages, N = N1 N2
-        const int n2 = c.dft_n / c.dft_n1;
-        if (n2 * c.dft_n1 != c.dft_n || c.dft_n1 > n2) return hipErrorInvalidValue;
-        // A quarter of the lanes with rows: 24 rows take 83 us against 156 (2^22
-        // samples, N = 1016 = 8 x 127, three frames) and 95 against 154 (N = 3336 =
-        // 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against
-        // 303 (N = 4072 = 8 x 509).
-        const int F = dft2_frames(c.dft_n, c.dft_n1);
-        const bool few = F * c.dft_n1 < 16;
-        const size_t lds = few ? dft2_few_lds_bytes(c.dft_n, c.dft_n1) : dft2_lds_bytes(c.dft_n, c.dft_n1);
+    const int N = c.dft_n, N1 = c.dft_n1;
+    if (N < 2 || !c.tw64 || c.K < 1) return hipErrorInvalidValue;
+    if (N1 > 0) {                       // two stages, N = N1 N2
+        if (N / N1 * N1 != N || N1 > N / N1) return hipErrorInvalidValue;
+        const bool few = dft2_takes_few(N, N1);
+        const size_t lds = few ? dft2_few_lds_bytes(N, N1) : dft2_lds_bytes(N, N1);
         if (lds > 160 * 1024) return hipErrorInvalidValue;
-        return launch_frames(a, few ? 1 : F, [&](const FftArgs& b, unsigned blocks) {
-            const dim3 grid(blocks, b.n_channels);
-            if (few) k_window_dft2_few<<<grid, 256, lds, st>>>(b);
-            else k_window_dft2<<<grid, 256, lds, st>>>(b);
+        return launch_frames(a, few ? 1 : dft2_frames(N, N1), [&](const FftArgs& b, unsigned blocks) {
+            launch(few ? k_window_dft2_few : k_window_dft2, dim3(blocks, b.n_channels), lds, b);
         });
     }
     const unsigned bz = (c.K + kDftBins - 1) / kDftBins;
     return launch_frames(a, kDftFrames, [&](const FftArgs& b, unsigned blocks) {
-        k_window_dft<<<dim3(blocks, b.n_channels, bz), 256, 0, st>>>(b);
+        launch(k_window_dft, dim3(blocks, b.n_channels, bz), 0, b);
+    });
+}
+
+hipError_t launch_dft(const FftArgs& a, hipStream_t st) {
+    return dft_launches(a, [&](void (*kernel)(FftArgs), dim3 grid, size_t lds, const FftArgs& b) {
+        kernel<<<grid, 256, lds, st>>>(b);
     });
 }
 

@@ -3,9 +3,10 @@
 //
 //   dft_driver N FRAMES K DTYPE MISALIGN N1 OUT.f32
 //
-// Runs k_window_dft (N1 = 0) or its two-stage form k_window_dft2 (N = N1 N2)
-// for frame length N (not a power of two) on FRAMES frames of one channel with
-// the launch shape and the argument fields the library uses (the FP64 table
+// Runs the launches of the library's dft_launches, k_window_dft (N1 = 0) or one of
+// the two-stage forms k_window_dft2 and k_window_dft2_few (N = N1 N2), for frame
+// length N (not a power of two) on FRAMES frames of one channel with the
+// argument fields the library uses (the FP64 table
 // exp(+2 pi j t / N) of N entries, K coefficients per frame), every buffer,
 // the dynamic LDS included, allocated to its exact size, and writes the
 // FRAMES x K complex outputs.  DTYPE 0 float32, 1 float64, 2 int16; MISALIGN 1 starts the
@@ -88,18 +89,13 @@ int main(int argc, char** argv) {
     c.out = out;
     c.out_chan_stride = frames * K;
     a.n_channels = 1;
-    // the library's launch shapes (launch_dft)
-    if (N1 > 0) {
-        if (N % N1 != 0 || N1 > N / N1) return 2;
-        const size_t lds = ps::dft2_lds_bytes(N, N1);
-        emu_dyn_smem = (char*)malloc(lds);
-        emu_launch([a] { ps::k_window_dft2(a); }, dim3((unsigned)frames, 1), 256);
-        free(emu_dyn_smem);
-    } else {
-        const dim3 grid((unsigned)((frames + ps::kDftFrames - 1) / ps::kDftFrames), 1,
-                        (unsigned)((K + ps::kDftBins - 1) / ps::kDftBins));
-        emu_launch([a] { ps::k_window_dft(a); }, grid, 256);
-    }
+    const hipError_t e =
+        ps::dft_launches(a, [](void (*kernel)(ps::FftArgs), dim3 grid, size_t lds, const ps::FftArgs& b) {
+            emu_dyn_smem = (char*)malloc(lds);
+            emu_launch([kernel, b] { kernel(b); }, grid, 256);
+            free(emu_dyn_smem);
+        });
+    if (e != hipSuccess) return 3;
     FILE* f = fopen(out_path, "wb");
     if (!f) return 4;
     fwrite(out, sizeof(float2), (size_t)(frames * K), f);
