@@ -754,12 +754,20 @@ hipError_t launch_frames(const FftArgs& a, int frames, Launch launch) {
     });
 }
 
-// Whether a two-stage length takes k_window_dft2_few.  With a quarter of the lanes
-// with rows or more k_window_dft2 is the faster: 24 rows take 83 us against 156 (2^22
-// samples, N = 1016 = 8 x 127, three frames) and 95 against 154 (N = 3336 =
-// 24 x 139), 8 rows 267 against 139 (N = 2008 = 8 x 251) and 727 against 303
-// (N = 4072 = 8 x 509).
-bool dft2_takes_few(int N, int N1) { return dft2_frames(N, N1) * N1 < 16; }
+// Whether a two-stage length takes k_window_dft2_few: by the rows that a block of
+// k_window_dft2 has for its 64 lanes, and by the bank conflicts of k_window_dft2_few,
+// whose rows of Y lie N2 + 1 pairs apart.  Measured at 335 lengths (2^22 samples,
+// time of k_window_dft2 over k_window_dft2_few): below 11 rows 1.1 to 3.5, with
+// N2 + 1 = 16 i 0.9 to 1.7; 11 to 13 rows 1.1 to 2.5, 16 i 0.5 to 0.7, 16 i + 8 0.85
+// and 1.14; 14 and 15 rows 1.1 to 1.5, 8 i 0.3 to 0.7; 16 rows 1.03 to 1.3, 4 i 0.8;
+// from 17 rows on 0.3 to 1.07, but 0.9 to 1.3 beyond N2 = 320 without conflicts,
+// where stage 2 is long and few blocks fit a CU (N = 7361: 484 us against 627).
+bool dft2_takes_few(int N, int N1) {
+    const int N2 = N / N1, rows = dft2_frames(N, N1) * N1, stride = (N2 + 1) % 16;
+    if (stride == 0) return rows < 11;
+    if (stride == 8) return rows < 14;
+    return rows < (stride % 4 == 0 ? 16 : 17) || N2 > 320;
+}
 
 // The direct transform's launches: launch(kernel, grid, bytes of LDS, arguments).
 template <typename Launch>

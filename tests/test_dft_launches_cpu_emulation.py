@@ -8,11 +8,13 @@ import pytest
 emu = pytest.importorskip("tests.test_fft_cpu_emulation")
 driver = emu.driver         # fixture
 
-# (N, frames, dtype, misaligned, N1): k_window_dft2_few at 8 x 251, 11 x 727 and 13 x 331;
-# k_window_dft2 with three and four frames a block and frame counts that are no
-# multiple of them (8 x 127, 15 x 19, 16 x 17) and one frame a block (17 x 307)
-INSTANCES = [(2008, 2, 2, 1, 8), (7997, 1, 0, 0, 11), (4303, 2, 1, 0, 13), (1016, 4, 0, 1, 8),
-             (1016, 3, 1, 0, 8), (285, 5, 2, 0, 15), (285, 1, 0, 0, 15), (272, 7, 0, 0, 16), (5219, 2, 0, 0, 17)]
+# (N, frames, dtype, misaligned, N1): k_window_dft2_few at 8 x 251, 11 x 727, 13 x 331
+# and, for its length, 17 x 433; k_window_dft2 with three and four frames a block and
+# frame counts that are no multiple of them (8 x 127, 15 x 19, 16 x 17), one frame a
+# block (17 x 307) and rows just above the rule's lines (11 x 479, 16 x 163)
+INSTANCES = [(2008, 2, 2, 1, 8), (7997, 1, 0, 0, 11), (4303, 2, 1, 0, 13), (7361, 1, 0, 1, 17), (1016, 4, 0, 1, 8),
+             (1016, 3, 1, 0, 8), (285, 5, 2, 0, 15), (285, 1, 0, 0, 15), (272, 7, 0, 0, 16), (5219, 2, 0, 0, 17),
+             (5269, 1, 2, 0, 11), (2608, 2, 0, 0, 16)]
 
 
 @pytest.mark.parametrize("N,frames,dtype,mis,n1", INSTANCES)
