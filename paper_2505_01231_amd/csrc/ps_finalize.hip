@@ -317,10 +317,11 @@ __device__ __forceinline__ void finalize_s1(const FinalizeArgs& p, const Finaliz
 
 // Every order's finalize in one launch: block ranges of S1, S2, S3 and S4 in
 // this order, so that the few latency-bound blocks of S1 and S2 run beside the
-// tiles.  Bound by the slots' bytes: S3's and S4's 512 slots of 128 and 64 KB
-// are 100 MB, read at 5.5 TB/s (10^6 samples, N = 1024, N_f = 200: 18 us; as
-// launches of their own 15 + 21 + 21 us; 2^26 samples, N = 4096, N_f = 512: 28
-// against 51 + 12 + 12 us, 51200 samples, N_f = 64: 7 against 23 us).
+// tiles.  Bound by the slots' bytes and latency: of S3's and S4's 512 slots of 128
+// and 64 KB at N_f = 200 the sub-blocks with grid points are 58 MB, read in 15 us
+// (10^6 samples, N = 1024); 2^26 samples, N = 4096, N_f = 512: 107 MB in 25 us;
+// 51200 samples, N_f = 64: 8 us.  A launch per order, on whole slots, took 57, 75
+// and 23 us.
 __global__ __launch_bounds__(256, 8) void k_finalize(FinalizeArgs p) {
     __shared__ union {
         VecLds vec;
@@ -336,9 +337,12 @@ __global__ __launch_bounds__(256, 8) void k_finalize(FinalizeArgs p) {
     else finalize_tile(p, tab, x, sm.tile);
 }
 
-// S3 or S4 alone, from kOwnLaunch blocks on: there a launch's 5 us are nothing
-// and the merged kernel's larger LDS and register demand costs 10 % (409
-// records of one chunk, N_f = 256, 65,440 blocks: 446 us against 512 merged).
+// S3 or S4 alone, from kOwnLaunch blocks on: there a launch's 6 us are nothing
+// and the merged kernel's larger LDS and register demand costs up to 13 %.
+// Interlaced records of one chunk (whose tiles all come here), S1 to S4, own
+// launches against one: 65,440 blocks an order (409 records, N_f = 256) 575 and
+// 647 us, 32,640 302 and 324; 32,768 at N_f = 64 383 and 381; 16,384 160 to 200 and
+// 170 to 183; 8,160 80 and 68.
 constexpr int64_t kOwnLaunch = 32768;
 
 __global__ __launch_bounds__(256, 8) void k_finalize_tiles(FinalizeArgs p, int role) {

@@ -182,7 +182,8 @@ struct CentreArgs {
 constexpr int kCentreRegs = 16;
 hipError_t launch_centre(const CentreArgs& a, hipStream_t s);
 // S1 and S2 alone: the chunk terms of every pair in s2_entry, nothing written
-// back.  Takes n_channels frames_held(m) <= 64, m <= 32.
+// back.  Every channel's frames of a chunk are held in registers, 16 or (m > 16)
+// 32 of them: up to 64 together.
 inline bool power_supported(int n_channels, int m) { return m <= 32 && n_channels * (m <= 16 ? 16 : 32) <= 64; }
 hipError_t launch_power(const CentreArgs& a, hipStream_t s);
 

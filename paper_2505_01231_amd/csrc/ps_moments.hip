@@ -14,15 +14,15 @@
 //
 // Each kernel accumulates, per grid point, the FP64 sums over its chunks of the
 // estimate (without its constant prefactor) and of its squared real and
-// imaginary parts; the finalize kernels turn those into the mean and the
-// Section 4.2 error bar.  The prefactors, the window sums and dt are applied
-// there.
+// imaginary parts, which become the mean and the Section 4.2 error bar, with
+// the prefactors, the window sums and dt applied: here for a tile that one block
+// takes whole (Emit), in the finalize kernels for the others.
 //
 // Work: each stage is one launch over every segment (record x combination);
 // a block takes its share of the segment's (tile, chunk) units as described at
 // Sched (whole tiles in rounds, plus one stream-K run over the remaining
-// tiles) and writes one partial-sum slot per piece (no atomics: the reduction
-// order is fixed).  Consecutive block ids are dealt round-robin over the 8 XCDs
+// tiles) and writes one partial-sum slot per piece, or the spectrum of a whole
+// tile (no atomics: the reduction order is fixed).  Consecutive block ids are dealt round-robin over the 8 XCDs
 // by the hardware; the ids are remapped so that each XCD sees a contiguous
 // range of blocks: the tiles of one round on one XCD then walk the same chunks
 // at the same time and share their coefficients in that XCD's L2.
@@ -1851,9 +1851,10 @@ __device__ __forceinline__ void s4_cross_item(const BatchArgs& p, const View& v,
     const int rowA = 16 * (w >> 1) + li, rowB = 16 * (w & 1) + li;
 
     // Loader role: (side, column, frame residue q): frames q, q + 4, q + 8.
-    // Columns c and c + 8 share an LDS bank at the 160-byte row stride, so the
-    // lanes of each 32-bit write group ({0-15, 32-47}, {16-31, 48-63}) take
-    // eight consecutive columns (as in k_s4_mfma_bf16).
+    // The lanes of each 32-bit write group ({0-15, 32-47}, {16-31, 48-63}) take
+    // four frames of eight consecutive columns: the words 3 f + i of four
+    // consecutive frames differ mod 4, and the pieces of one word in eight
+    // consecutive columns are permuted apart (op_word), so no two share a bank.
     const int side = __builtin_amdgcn_readfirstlane(tid >> 7);    // uniform per wave
     const int col = 16 * (w & 1) + (((lane >> 2) & 3) | (((lane >> 5) & 1) << 2) | (((lane >> 4) & 1) << 3));
     const int q = tid & 3;
