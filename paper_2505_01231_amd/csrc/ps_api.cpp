@@ -188,41 +188,41 @@ struct ps_plan_s {
         const int8_t* q = &c4[4 * i];
         return s4_shift == 0 && q[0] == q[2] && q[1] == q[3];
     }
-    // Combination (a, b, d, c) that the matrix-core cross-channel kernel forms
-    // together with combination i = (a, b, c, d) (same Grams), or -1; for the
-    // second of a pair, `first` is set and the index is the first's.
-    int s4_pair(int i, bool& first) const {
-        const int8_t* q = &c4[4 * i];
-        first = true;
-        // (chunks of several frame batches: the pair form's loop does not fit the registers)
-        if (precision != PS_PREC_BF16X3 || s4_shift != 0 || m > ps::kPairFrames) return -1;
-        if (q[0] == q[1] || q[2] == q[3] || s4_sym(i)) return -1;
-        // the k-th combination (a, b, c, d) goes with the k-th (a, b, d, c)
-        int nth = 0, same = 0;
-        auto is = [&](int j, int c, int d) {
-            const int8_t* r = &c4[4 * j];
-            return r[0] == q[0] && r[1] == q[1] && r[2] == c && r[3] == d;
-        };
-        for (int j = 0; j < i; ++j) nth += is(j, q[2], q[3]);
-        for (int j = 0; j < n4(); ++j)
-            if (is(j, q[3], q[2]) && same++ == nth) {
-                if (s4_sym(j)) return -1;
-                first = i < j;
-                return j;
-            }
-        return -1;
-    }
-    // Relative cost of a unit of combination i in the cross-channel kernels,
-    // in tenths, for the work split: where channels coincide, Grams are shared
-    // (see k_s4_cross_mfma; per chunk 40 matrix instructions and 200 FP64 ones
-    // in the general form, 44 and 310 for a pair, 24 and 160 with a == b or
-    // c == d, 16 and 130 with both).
-    int s4x_cost(int i) const {
-        const int8_t* q = &c4[4 * i];
-        bool first;
-        if (precision != PS_PREC_BF16X3 || s4_shift != 0) return 10;
-        if (s4_pair(i, first) >= 0) return 13;
-        return q[0] == q[1] && q[2] == q[3] ? 6 : q[0] == q[1] || q[2] == q[3] ? 8 : 10;
+    // What the matrix-core cross-channel kernel makes of combination i = (a, b, c, d),
+    // found once per plan (set_s4_forms).
+    struct S4Form {
+        // Combination (a, b, d, c) that the kernel forms together with it (same
+        // Grams), or -1; the first of the two is the one that names both.
+        int pair = -1;
+        bool first = true;
+        // Relative cost of a unit, in tenths, for the work split: where channels
+        // coincide, Grams are shared (see k_s4_cross_mfma; per chunk 40 matrix
+        // instructions and 200 FP64 ones in the general form, 44 and 310 for a pair,
+        // 24 and 160 with a == b or c == d, 16 and 130 with both).
+        int cost = 10;
+    };
+    std::vector<S4Form> s4_form;
+    void set_s4_forms() {
+        s4_form.assign(n4(), S4Form{});
+        if (precision != PS_PREC_BF16X3 || s4_shift != 0) return;
+        std::array<std::vector<int>, 256> at;       // combinations by their channels, in order
+        auto key = [](int a, int b, int c, int d) { return ((a * 4 + b) * 4 + c) * 4 + d; };
+        for (int i = 0; i < n4(); ++i) at[key(c4[4 * i], c4[4 * i + 1], c4[4 * i + 2], c4[4 * i + 3])].push_back(i);
+        std::array<size_t, 256> seen{};
+        for (int i = 0; i < n4(); ++i) {
+            const int8_t* q = &c4[4 * i];
+            S4Form& f = s4_form[i];
+            const bool ab = q[0] == q[1], cd = q[2] == q[3];
+            f.cost = ab && cd ? 6 : ab || cd ? 8 : 10;
+            // the k-th combination (a, b, c, d) goes with the k-th (a, b, d, c)
+            const size_t nth = seen[key(q[0], q[1], q[2], q[3])]++;
+            const std::vector<int>& other = at[key(q[0], q[1], q[3], q[2])];
+            // (chunks of several frame batches: the pair form's loop does not fit the registers)
+            if (ab || cd || m > ps::kPairFrames || s4_sym(i) || nth >= other.size() || s4_sym(other[nth])) continue;
+            f.pair = other[nth];
+            f.first = i < f.pair;
+            f.cost = 13;
+        }
     }
     // Frame lengths: fc[0] mirrors the fields above (same device tables);
     // fc[1..] are the further frame lengths records may carry.
@@ -603,11 +603,10 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
                 if (!s2_direct(i, r)) U2.push_back((int64_t)kblocks * Np);
             for (int i = 0; i < p->n3(); ++i) U3.push_back(fc.n_tiles[p->s3_sym(i) ? ps::kSym64 : ps::kFull64] * Np);
             for (int i = 0; i < p->n4(); ++i) {
-                bool first = true;
+                const ps_plan_s::S4Form& form = p->s4_form[i];
                 if (p->s4_single(i)) U4s.push_back(fc.n_tiles[ps::kSym64] * Np);
-                else if (p->s4_pair(i, first) < 0 || first)
-                    U4x.push_back(
-                        weighted(fc.n_tiles[p->s4_sym(i) ? ps::kSym32 : ps::kFull32] * Np, p->s4x_cost(i)));
+                else if (form.first)
+                    U4x.push_back(weighted(fc.n_tiles[p->s4_sym(i) ? ps::kSym32 : ps::kFull32] * Np, form.cost));
             }
         }
         const int64_t L2 = units_per_block(U2, 4LL * p->n_cu);
@@ -727,12 +726,12 @@ void build_batch(const ps_plan_s* p, const ps_record* recs, int n, const ps_outp
             for (int i = 0; i < p->n4(); ++i) {
                 ps::Seg sg = base;
                 const bool single = p->s4_single(i), sym = p->s4_sym(i);
-                bool first = true;
-                const int pair = single ? -1 : p->s4_pair(i, first);
+                const int pair = single ? -1 : p->s4_form[i].pair;
+                const bool first = single || p->s4_form[i].first;
                 sg.tiles = single ? ps::kSym64 : (sym ? ps::kSym32 : ps::kFull32);
                 sg.tile_tab = fc.d_tiles[sg.tiles];
                 sg.n_tiles = fc.n_tiles[sg.tiles];
-                sg.blocks = seg_blocks(sg.n_tiles, q.Np, single ? L4s : L4x, per_chunk, single ? 10 : p->s4x_cost(i));
+                sg.blocks = seg_blocks(sg.n_tiles, q.Np, single ? L4s : L4x, per_chunk, single ? 10 : p->s4_form[i].cost);
                 for (int j = 0; j < 4; ++j) sg.ch[j] = p->c4[4 * i + j];
                 sg.ncomp = single ? 2 : 4;
                 if (single && k.op_chunks > 0) {
@@ -1066,6 +1065,8 @@ ps_status ps_plan_create(const ps_config* cfg, ps_plan_t* out) {
                 return fail(PS_E_INVALID_ARG, "combination refers to channel %d of %d", ch, p->C);
             }
     }
+
+    p->set_s4_forms();
 
     // Tables of the plan's frame length (class 0): the twiddle layout depends
     // on the transform (complex signals: the tables of a real transform of
