@@ -294,9 +294,9 @@ ps_status ps_execute(ps_plan_t plan, const ps_record* recs, int32_t n_rec, void*
  * address is resolved for a device when the first plan is created there).
  * The call allocates nothing: no device memory, no pinned host memory, no
  * events (stage timing is not recorded).  Limits: ps_workspace_size() of the
- * records must not exceed PS_STATIC_SCRATCH_BYTES, and their work tables must
- * fit the plan's pinned staging (4 MiB; about 30,000 record-combination
- * segments); otherwise PS_E_WORKSPACE and nothing is enqueued.
+ * records, less S2's chunk terms, must not exceed PS_STATIC_SCRATCH_BYTES, and
+ * their work tables must fit the plan's pinned staging (4 MiB; about 30,000
+ * record-combination segments); otherwise PS_E_WORKSPACE and nothing is enqueued.
  * PS_E_INVALID_ARG when no plan was ever created on the current device.  All
  * calls on one GPU share its array, which keeps the last call's contents
  * (nothing in it needs to start at zero): calls that overlap on one GPU
